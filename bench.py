@@ -168,6 +168,7 @@ KERNEL_SOURCES = {
     "gtp_small.hip": ["gen_small_consts.cpp", "gtp_small.hpp"],
     "gtp_escn.hip": ["gen_small_consts.cpp", "gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
     "gtp_wave.hip": ["gtp_fft.hpp"],
+    "gtp_mfma.hip": ["gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp"],
     "gtp_escn_wave.hip": ["gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
 }
 
@@ -186,7 +187,9 @@ def padded_kernel(L1: int, L2: int, Lout: int):
     if A <= 8:
         return f"k_full_small_pad<{A}>", "alu", "gtp_small.hip"
     W = 16 if A <= 16 else (32 if A <= 32 else 64)
-    return ("k_full_wave4" if W > 32 else "k_full_wave") + f" (padded to L = {W})", "mfma", "gtp_wave.hip"
+    if W > 32:
+        return f"k_full_wave4 (padded to L = {W})", "mfma", "gtp_wave.hip"
+    return f"k_full_mfma (padded to L = {W})", "mfma", "gtp_mfma.hip"
 
 
 def fused_backward(degrees, conv: str = "auto") -> bool:
@@ -202,7 +205,7 @@ def dominant_kernel(workload: str, L: int, escn: bool = False, conv: str = "auto
             and not (degrees[0] == degrees[1] == degrees[2] and degrees[0] in (16, 32, 64)):
         return padded_kernel(*degrees)
     if conv == "fft" and workload in ("sweep", "highdeg") and L in (16, 32, 64):
-        return ("k_full_wave4_fft" if L > 32 else "k_full_wave (FFT)"), "alu", "gtp_wave.hip"
+        return ("k_full_wave4_fft" if L > 32 else "k_full_wave_fft"), "alu", "gtp_wave.hip"
     if escn:
         # both kernels of the step (rotation matrices, then the product): one unit
         if L == 16:
@@ -213,7 +216,7 @@ def dominant_kernel(workload: str, L: int, escn: bool = False, conv: str = "auto
         # pair products (thread per product) and the mix on the matrix cores in one kernel
         return "k_mix_fused", "alu", "gtp_small.hip"
     if workload in ("sweep", "highdeg", "edge16") and (L >= 16 or workload == "highdeg"):
-        return ("k_full_wave4" if L > 32 else "k_full_wave"), "mfma", "gtp_wave.hip"
+        return ("k_full_wave4", "mfma", "gtp_wave.hip") if L > 32 else ("k_full_mfma", "mfma", "gtp_mfma.hip")
     if workload == "manybody":
         return "k_self_stepwise_small", "alu", "gtp_small.hip"
     return "k_full_small", "alu", "gtp_small.hip"
@@ -599,7 +602,7 @@ def measure_roofs(torch, gtp):
 def l32_sweep(args, torch, gtp, inputs):
     """The degree-32 product measured in the same run as the edge workload:
     the L = 32 degree sweep (B = 2048 x C = 128 products, iid N(0,1), fp32,
-    the matrix-core kernel k_full_wave<32>), with the same warmup and step
+    the matrix-core kernel k_full_mfma<32>), with the same warmup and step
     counts, after the edge workload's timed region: its kernel time on the
     launch stream, its fraction of the fp32 peak at the kernel's flop count
     and its HBM traffic when the committed counters match the sources (its
@@ -621,11 +624,11 @@ def l32_sweep(args, torch, gtp, inputs):
     torch.cuda.synchronize()
     kernel_ms = ev0.elapsed_time(ev1) / args.steps
     achieved = alg_flops[0] * products / (kernel_ms * 1e-3) / 1e12
-    return {"workload": desc["workload"], "kernel": "k_full_wave", "kernel_ms": round(kernel_ms, 5),
+    return {"workload": desc["workload"], "kernel": "k_full_mfma", "kernel_ms": round(kernel_ms, 5),
             "products_per_s": products / (kernel_ms * 1e-3),
             "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "alg_flops_per_product": alg_flops[0],
-                         "traffic": load_traffic("sweep_L32", "gtp_wave.hip"),
+                         "traffic": load_traffic("sweep_L32", "gtp_mfma.hip"),
                          "alg_bytes_per_launch": alg_bytes * products}}
 
 

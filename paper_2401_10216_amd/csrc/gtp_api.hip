@@ -19,6 +19,7 @@
 #include "../../include/gtp.h"
 #include "gtp_device.hpp"
 #include "gtp_escn.hpp"
+#include "gtp_mfma_tables.hpp"
 #include "gtp_probe.hpp"
 #include "gtp_small.hpp"
 #include "gtp_tables.hpp"
@@ -32,6 +33,8 @@ struct gtp_plan_ {
   int conv = GTP_CONV_DFT;
   bool force_generic = false;
   gtp::Tables tab;
+  std::vector<uint16_t> mfx;  // and the index images of the plan's own row lengths (padded plans too)
+  gtp::MfmaImages mf;         // operand images of the split-operand kernel (L1 = L2 = Lout in {16, 32})
   gtp::EscnHost esc;  // rotated-frame convolution tables (L1 = L2 = Lout <= 8)
   std::vector<float*> dbufs;
   gtp::DevTables dev{};
@@ -160,6 +163,20 @@ gtp_status upload(gtp_plan_* p, long fail_at) {
   d.TWR = d.SMP = d.SM0P = d.WP = nullptr;
   d.XMAP = nullptr;
   d.XQUADS = t.XQUADS;
+  d.MF = d.MFX = nullptr;
+  d.MS = nullptr;
+  d.mf_kw = p->mf.kw;
+  if (!p->mf.f.empty() && (s = up(&p->mf.f, nullptr, &d.MS)) != GTP_OK) return s;
+  for (auto [src, dst] : {std::pair<const std::vector<uint16_t>*, const uint16_t**>{&p->mf.h, &d.MF}, {&p->mfx, &d.MFX}}) {
+    if (src->empty()) continue;
+    void* dm = nullptr;
+    hipError_t e = dmalloc(&dm, src->size() * sizeof(uint16_t));
+    if (e != hipSuccess) return fail(GTP_ERR_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
+    p->dbufs.push_back(static_cast<float*>(dm));
+    e = hipMemcpy(dm, src->data(), src->size() * sizeof(uint16_t), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+    *dst = static_cast<const uint16_t*>(dm);
+  }
   d.phi_fft = p->conv == GTP_CONV_FFT ? 1 : 0;
   p->escd = gtp::EscnDev{nullptr, nullptr, 0, 0, 0, nullptr, nullptr, nullptr};
   if (p->esc.NPAIR) {
@@ -257,6 +274,10 @@ gtp_status make_plan(gtp_plan* out, int L1, int L2, int Lout, unsigned flags, in
     // and 16 (degrees 9..15 run on a 16-plan's tables)
     if (L1 == L2 && L2 == Lout && ((L1 >= 1 && L1 <= 8) || L1 == gtp::kEscnWaveL))
       p->esc = gtp::build_escn_tables(p->tab);
+    if (p->conv == GTP_CONV_DFT) p->mf = gtp::build_mfma_images(p->tab);
+    const int WF = p->mf.h.empty() ? pad_wave_degree(L1, L2, Lout) : L1;
+    if (p->conv != GTP_CONV_DIRECT && (WF == 16 || WF == 32))
+      p->mfx = gtp::build_mfma_index(WF, gtp::nsh(L1), gtp::nsh(L2), gtp::nsh(Lout));
   } catch (const std::bad_alloc&) {
     return fail(GTP_ERR_ALLOC, "table allocation failed");
   } catch (const std::exception& e) {
@@ -350,6 +371,8 @@ gtp_status run_product(gtp_plan p, const void* x1, int it1, const void* x2, int 
   if (!p->force_generic) {
     e = gtp::launch_full_small(p->dev, x1, it1, x2, it2, n, y, 0, wt, st, &done);
     if (done) return e == hipSuccess ? GTP_OK : hip_fail(e, what);
+    e = gtp::launch_full_mfma(p->dev, x1, it1, x2, it2, n, y, wt, st, &done);
+    if (done) return e == hipSuccess ? GTP_OK : hip_fail(e, what);
     e = gtp::launch_full_wave(p->dev, x1, it1, x2, it2, n, y, wt, st, &done);
     if (done) return e == hipSuccess ? GTP_OK : hip_fail(e, what);
     if (!wt.on) {
@@ -373,6 +396,10 @@ gtp_status run_product(gtp_plan p, const void* x1, int it1, const void* x2, int 
           const gtp_status s = cached_plan(W, W, W, GTP_CONV_DFT, &q);
           if (s != GTP_OK) return s;
         }
+        gtp::DevTables qd = q->dev;  // the padded degree's tables, this plan's rows
+        qd.MFX = p->dev.MFX;
+        e = gtp::launch_full_mfma(qd, x1, it1, x2, it2, n, y, wt, st, &done, k1, k2, ko);
+        if (done) return e == hipSuccess ? GTP_OK : hip_fail(e, what);
         e = gtp::launch_full_wave(q->dev, x1, it1, x2, it2, n, y, wt, st, &done, k1, k2, ko);
         if (done) return e == hipSuccess ? GTP_OK : hip_fail(e, what);
       }

@@ -30,6 +30,13 @@ struct DevTables {
   const float* WP;    // [pass][it][lane][8]    theta analysis weights
   const int* XMAP;    // [lane][k]              LDS slot of input coefficient lane + 64 k
   int XQUADS;
+  // Operand images of the split-operand matrix-core kernel
+  // (gtp_mfma_tables.hpp; L1 = L2 = Lout in {16, 32}, null otherwise) and its
+  // theta-analysis scale.
+  const float* MS;
+  const uint16_t* MF;
+  const uint16_t* MFX;  // index images of the plan's own row lengths
+  int mf_kw;
   int phi_fft;        // 1: the matrix-core kernel's phi transforms by radix-2 FFT (GTP_CONV_FFT)
 };
 
@@ -127,6 +134,11 @@ hipError_t launch_full_small_padded(int L, const void* x1, int it1, int k1, cons
 hipError_t launch_full_wave(const DevTables& t, const void* x1, int it1, const void* x2, int it2, int64_t n,
                             float* y, const DegWeights& wt, hipStream_t s, bool* supported, int k1 = 0, int k2 = 0,
                             int ko = 0);
+// Four products per workgroup, the transforms as contractions of split operands, for
+// L1 = L2 = Lout = L in {16, 32}, and padded to them (k1, k2, ko as above);
+// *supported = false otherwise and for the type pairs launch_full_wave lacks.
+hipError_t launch_full_mfma(const DevTables& t, const void* x1, int it1, const void* x2, int it2, int64_t n, float* y,
+                            const DegWeights& wt, hipStream_t s, bool* supported, int k1 = 0, int k2 = 0, int ko = 0);
 // Workgroup-per-product fused kernel, any degrees (nu = 0: x1 * x2;
 // nu >= 2: x1^nu with the plan built for U = nu * L).
 hipError_t launch_full_generic(const DevTables& t, const void* x1, int type1, const void* x2, int type2,

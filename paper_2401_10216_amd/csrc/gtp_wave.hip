@@ -1,5 +1,6 @@
-// Wave-per-product fused Gaunt tensor product on the matrix cores, for
-// L1 = L2 = Lout = L in {16, 32} (gfx950).
+// Wave-per-product fused Gaunt tensor products (gfx950): the fp32 matrix-core
+// kernel of L1 = L2 = Lout = 64 (four waves per product; also every triple
+// padded to it) and the radix-FFT variants of degrees 16, 32 and 64.
 //
 // Same sampled pipeline as the small-degree kernel (Sec. 3.2 with the
 // convolution theorem): theta nodes t_j = j pi / (2L+1), taken as mirror
@@ -834,16 +835,6 @@ __device__ __forceinline__ void store_out(float* y, int64_t P, int ko, int i, fl
     y[P * K + i] = v;
   }
 }
-// The same from the product's own output row yr (wave-uniform) and the
-// coefficient's byte offset in it.
-template <bool PAD>
-__device__ __forceinline__ void store_row(float* yr, int ko, unsigned byte_off, float v) {
-  if constexpr (PAD) {
-    if (byte_off < 4u * unsigned(ko)) st_row_bytes(yr, byte_off, v);
-  } else {
-    st_row_bytes(yr, byte_off, v);
-  }
-}
 // A padded plan's outputs above degree L (when its Lout > L) are zeros.
 template <int K>
 __device__ __forceinline__ void zero_tail(float* y, int64_t P, int ko, int tid, int nth) {
@@ -914,32 +905,29 @@ __device__ __forceinline__ const unsigned* row_out_table() {
   }
 }
 
-// L in {16, 32}: one wave per product; theta analysis accumulates in
-// registers after every pass.  FFT: the phi transforms by radix-2 FFTs
-// (phi_fft) instead of the direct-DFT contractions on the matrix cores.
-// PAD: a plan of lower degrees padded to L (rows of k1, k2 inputs, ko outputs;
-// see stage_x and store_row).
-template <int L, typename T1, typename T2, bool WGT, bool FFT, bool PAD = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FFT ? 1 : 3))) void k_full_wave(
+// The radix-FFT variant (phi_fft) of L in {16, 32}: one wave per product; theta
+// analysis accumulates in registers after every pass.
+template <int L, typename T1, typename T2, bool WGT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) void k_full_wave_fft(
     const T1* __restrict__ x1, const T2* __restrict__ x2, float* __restrict__ y, int64_t n, DevTables t,
-    DegWeights wt, int k1, int k2, int ko) {
+    DegWeights wt) {
   using G = WGeo<L>;
   static_assert(L % 16 == 0 && L <= 32, "L must be 16 or 32");
   constexpr int NJ = G::NJ, NP = G::NP;
   constexpr int NMP2 = G::NMP2, K = G::K, PASSES = G::PASSES, NROW = G::NROW, NIT = G::NIT;
   // the moments first: their reads then carry small immediate offsets
-  constexpr int FFTF = FFT ? 2 * (FGeo<L>::AC + FGeo<L>::TC) : 0;  // the FFT variant's spectra and T
+  constexpr int FFTF = 2 * (FGeo<L>::AC + FGeo<L>::TC);  // the spectra and T
   __shared__ __align__(16) float lds[G::EOP + G::XQ * 4 + FFTF];
   lds_poison(lds, G::EOP + G::XQ * 4 + FFTF);
   float* const eo = lds;
   float* const xs = lds + G::EOP;
   float2* const fa = reinterpret_cast<float2*>(lds + G::EOP + G::XQ * 4);
-  float2* const ft = fa + (FFT ? FGeo<L>::AC : 0);
+  float2* const ft = fa + FGeo<L>::AC;
 
   const int lane = threadIdx.x;
   if (int64_t(blockIdx.x) >= n) return;  // whole-wave exit (one product per workgroup)
   const int64_t P = xcd_product(blockIdx.x, n);
-  stage_x<L, WGT, PAD>(xs, x1, x2, P, lane, t.XMAP, wt, k1, k2);
+  stage_x<L, WGT>(xs, x1, x2, P, lane, t.XMAP, wt);
 
   const __amdgpu_buffer_rsrc_t WPr = table_rsrc(t.WP, PASSES * (NIT + 1) * 64 * 8);
   const __amdgpu_buffer_rsrc_t Wr = table_rsrc(t.WT, NJ * t.ntW);
@@ -963,7 +951,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FFT ? 1 : 3)
     const WaveCtx<L> w(lnp, reinterpret_cast<const float4*>(xs), t);
     f4 o[1][4];
     float zz;
-    w.template pass<FFT>(pu, o, zz, fa);
+    w.template pass<true>(pu, o, zz, fa);
     // this pass's row offsets (loaded here, not held across the passes:
     // that would keep NIT more registers live through the contractions)
     int er[NIT];
@@ -986,12 +974,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FFT ? 1 : 3)
     });
     const float4 wz0 = tload4_s(WPr, lane * 32, wbase + NIT * 64 * 32);
     const float4 wz1 = tload4_s(WPr, lane * 32 + 16, wbase + NIT * 64 * 32);
-    if constexpr (FFT) {
-      __syncthreads();  // the spectra of all 16 column nodes are in LDS
-      w.phi_fft(eo, fa, ft);
-    } else {
-      w.store_moments(eo, o, zz);
-    }
+    __syncthreads();  // the spectra of all 16 column nodes are in LDS
+    w.phi_fft(eo, fa, ft);
     __syncthreads();
 
     if (lane <= L) {
@@ -1035,14 +1019,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FFT ? 1 : 3)
   const float f = p1 * p2 * float(NP);
   const float fN = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 0));  // wave-uniform
   const float fS = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), 8));
-  float* const yr = y + P * (PAD ? ko : K);  // this product's output row (wave-uniform)
+  float* const yr = y + P * K;  // this product's output row (wave-uniform)
   if (lane <= L) {
     const int l = lane;
     y0 = fmaf(tload(Wr, wr0), fN + ((l & 1) ? -fS : fS), y0);
     if constexpr (WGT) {
       if (wt.wo) y0 *= wt.wo[weight_row(wt, P) * (L + 1) + l];
     }
-    store_row<PAD>(yr, ko, unsigned(4 * (l * l + l)), y0);
+    st_row_bytes(yr, unsigned(4 * (l * l + l)), y0);
   }
   int ln = lane;
   asm volatile("" : "+v"(ln));
@@ -1058,11 +1042,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FFT ? 1 : 3)
         row_lm(q, l, m);
         if (wt.wo) wl = wt.wo[weight_row(wt, P) * (L + 1) + l];
       }
-      store_row<PAD>(yr, ko, ro & 0xffffu, yc[it] * wl);
-      store_row<PAD>(yr, ko, ro >> 16, ys[it] * wl);
+      st_row_bytes(yr, ro & 0xffffu, yc[it] * wl);
+      st_row_bytes(yr, ro >> 16, ys[it] * wl);
     }
   });
-  if constexpr (PAD) zero_tail<K>(y, P, ko, lane, 64);
 }
 
 // L = 64: four waves per product (256 threads), wave v runs passes 2v and
@@ -1295,9 +1278,7 @@ template <int L, typename T1, typename T2, bool WGT, bool PAD = false>
 hipError_t launch_wave_typed(const void* x1, const void* x2, int64_t n, float* y, const DevTables& t,
                              const DegWeights& wt, hipStream_t s, int k1 = WGeo<L>::K, int k2 = WGeo<L>::K,
                              int ko = WGeo<L>::K) {
-  // the radix-FFT phi transforms where the plan asks for them and a
-  // one-wave kernel exists (L = 16, 32)
-  const bool fft = t.phi_fft != 0;
+  const bool fft = t.phi_fft != 0;  // the radix-FFT phi transforms where the plan asks for them
   using G = WGeo<L>;
   // at most 2^30 workgroups per launch
   for (int64_t p0 = 0; p0 < n; p0 += (int64_t(1) << 30)) {
@@ -1308,12 +1289,7 @@ hipError_t launch_wave_typed(const void* x1, const void* x2, int64_t n, float* y
     DegWeights w = wt;
     w.pbase += p0;  // the chunk's products start at p0
     if constexpr (G::NW == 1) {
-      if (fft && !PAD)
-        hipLaunchKernelGGL((k_full_wave<L, T1, T2, WGT, true>), dim3(unsigned(nn)), dim3(64), 0, s, a, b, yy, nn, t, w,
-                           k1, k2, ko);
-      else
-        hipLaunchKernelGGL((k_full_wave<L, T1, T2, WGT, false, PAD>), dim3(unsigned(nn)), dim3(64), 0, s, a, b, yy, nn,
-                           t, w, k1, k2, ko);
+      hipLaunchKernelGGL((k_full_wave_fft<L, T1, T2, WGT>), dim3(unsigned(nn)), dim3(64), 0, s, a, b, yy, nn, t, w);
     } else if (fft && !PAD) {
       hipLaunchKernelGGL((k_full_wave4_fft<L, T1, T2, WGT>), dim3(unsigned(nn)), dim3(G::NTH), 0, s, a, b, yy, nn, t,
                          w);
@@ -1336,7 +1312,14 @@ hipError_t launch_wave_one(const DevTables& t, const void* x1, int it1, const vo
                            float* y, const DegWeights& wt, hipStream_t s, bool* supported, int k1, int k2, int ko) {
   // the scatter map's slots must fit the kernel's LDS image
   if (t.XQUADS != WGeo<L>::XQ) return hipErrorInvalidValue;
-  if (ko > 0) {
+  if constexpr (L < 64) {
+    // degrees 16 and 32: the radix-FFT variant only, full rows
+    if (!t.phi_fft || ko > 0) {
+      *supported = false;
+      return hipSuccess;
+    }
+  }
+  if constexpr (L == 64) if (ko > 0) {
     if (wt.on || k1 > WGeo<L>::K || k2 > WGeo<L>::K) {
       *supported = false;
       return hipSuccess;

@@ -1,0 +1,92 @@
+"""The split-operand matrix-core product kernel (degrees 16, 32 and every
+triple padded to them): its operand and index images on the CPU, and the
+kernel at the sizes and values where it can go wrong on the GPU."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gtp_oracle as O  # noqa: E402
+from paper_2401_10216_amd import gtp  # noqa: E402
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2401_10216_amd", "csrc")
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_operand_and_index_images(tmp_path):
+    exe = str(tmp_path / "mfma_host")
+    r = subprocess.run(["g++", "-O1", "-std=c++17", f"-I{CSRC}", "-o", exe,
+                        os.path.join(ROOT, "tests", "mfma_host_main.cpp"), os.path.join(CSRC, "gtp_mfma_tables.cpp"),
+                        os.path.join(CSRC, "gtp_tables.cpp")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout
+
+
+def _check(L1, L2, Lout, a, b, offset=0, what=""):
+    """gtp_full of rows a, b (values already of the call's type) against the oracle, per product."""
+    n = a.shape[0]
+    plan = gtp.Plan(L1, L2, Lout)
+
+    def dev(x):  # `offset` elements off the allocation's alignment
+        buf = torch.empty(x.numel() + offset, dtype=x.dtype, device="cuda")
+        v = buf[offset:].view(n, 1, x.shape[-1])
+        v.copy_(x.view(n, 1, -1))
+        return v
+
+    y = gtp.gtp_full(plan, dev(a), dev(b)).cpu().numpy().astype(np.float64)[:, 0]
+    ref = O.gtp_grid(a.double().numpy(), b.double().numpy(), L1, L2, Lout)
+    err = O.max_rel_err(y, ref)
+    print(what, (L1, L2, Lout), n, f"err={err:.2e}", flush=True)
+    assert err <= 1e-6, err  # fp32: worst errors of these kernels are 1e-7 of the output norm
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("degrees", [(16, 16, 16), (32, 32, 32), (9, 9, 9), (17, 20, 25), (0, 16, 16), (10, 3, 7),
+                                     (5, 6, 30), (31, 1, 32), (16, 16, 40)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_edges_of_groups_and_rows(degrees, dtype):
+    """Batches about the four products of a group; rows off 16-byte (4-byte) alignment."""
+    L1, L2, Lout = degrees
+    g = torch.Generator().manual_seed(7)
+    for n, offset in ((1, 0), (3, 1), (4, 0), (4, 1), (5, 0), (11, 2)):
+        a = torch.randn((n, (L1 + 1) ** 2), generator=g).to(dtype)
+        b = torch.randn((n, (L2 + 1) ** 2), generator=g).to(dtype)
+        _check(L1, L2, Lout, a, b, offset, f"{dtype} n={n} offset={offset}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L", [16, 32])
+def test_scales_and_special_values(L):
+    """Magnitudes over the fp32 range, sparse and concentrated rows, zeros, and a row of NaN or Inf beside others."""
+    K = (L + 1) ** 2
+    g = torch.Generator().manual_seed(8)
+    a, b = torch.randn((12, K), generator=g), torch.randn((12, K), generator=g)
+    a[0] *= 1e25  # the sum of squares overflows
+    b[0] *= 1e-25  # and underflows
+    a[1] *= 1e-30
+    b[1] *= 1e20
+    a[2] = 0.0
+    a[2, K - 1] = 3.0  # single coefficients
+    b[3] = 0.0
+    b[3, 0] = -2.0
+    a[4] = torch.as_tensor(O.real_sh(L, np.array([0.3]), np.array([1.1]))[0]) if hasattr(O, "real_sh") else a[4]
+    b[4] = a[4]  # concentrated at one direction: the largest products the scales allow for
+    a[5, L * L:] = 0.0
+    b[6, : L * L] = 0.0
+    a[7] *= 1e-12
+    _check(L, L, L, a, b, 0, "scales")
+    a[8] = 0.0
+    a[9, 5] = float("nan")
+    b[10, 7] = float("inf")
+    y = gtp.gtp_full(gtp.Plan(L, L, L), a.cuda().view(12, 1, K), b.cuda().view(12, 1, K)).cpu()[:, 0]
+    assert (y[8] == 0).all()
+    assert y[9].isnan().any() and not y[10].isfinite().all()
+    ok = [0, 1, 2, 3, 4, 5, 6, 7, 11]  # the same group's other rows are untouched
+    ref = O.gtp_grid(a[ok].double().numpy(), b[ok].double().numpy(), L, L, L)
+    assert O.max_rel_err(y[ok].numpy().astype(np.float64), ref) <= 1e-6
