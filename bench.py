@@ -165,7 +165,7 @@ def nsh(L):
 # kernel files (build-time constants, their tables)
 SHARED_SOURCES = ["gtp_ct.hpp", "gtp_device.hpp", "gtp_tables.cpp", "gtp_tables.hpp"]
 KERNEL_SOURCES = {
-    "gtp_small.hip": ["gen_small_consts.cpp", "gtp_small.hpp"],
+    "gtp_small.hip": ["gen_small_consts.cpp", "gtp_small.hpp", "gtp_small_core.hpp"],
     "gtp_escn.hip": ["gen_small_consts.cpp", "gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
     "gtp_wave.hip": ["gtp_fft.hpp"],
     "gtp_mfma.hip": ["gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp"],

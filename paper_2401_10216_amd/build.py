@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "libgtp.so")
 
 HIP_SOURCES = ["gtp_api.hip", "gtp_small.hip", "gtp_wave.hip", "gtp_mfma.hip", "gtp_generic.hip", "gtp_escn.hip", "gtp_escn_wave.hip",
                "gtp_mix.hip",
-               "gtp_probe.hip", "gtp_wgrad.hip"]
+               "gtp_probe.hip", "gtp_wgrad.hip", "gtp_wbwd.hip"]
 CPP_SOURCES = ["gtp_tables.cpp", "gtp_escn_tables.cpp", "gtp_mfma_tables.cpp"]
 ARCH = "gfx950"
 # Packed fp32 VALU forms stay off: plain fp32 FMAs only.
@@ -89,7 +89,7 @@ def build(verbose: bool = False, poison: bool = True) -> str:
     t0 = time.time()
     failed = []
     running = []
-    pending = sorted(jobs, key=lambda j: 0 if "gtp_small" in j[1] else 1)  # the longest first
+    pending = sorted(jobs, key=lambda j: 0 if "gtp_small" in j[1] else 1 if "gtp_wbwd" in j[1] else 2)  # the longest first
     while pending or running:
         while pending and len(running) < 8:
             cmd, obj, vi = pending.pop(0)

@@ -23,6 +23,7 @@
 #include "gtp_probe.hpp"
 #include "gtp_small.hpp"
 #include "gtp_tables.hpp"
+#include "gtp_wbwd.hpp"
 
 struct gtp_plan_ {
   int L1 = 0, L2 = 0, Lout = 0;
@@ -799,6 +800,41 @@ gtp_status gtp_full_weighted_backward(gtp_plan p, const void* x1, const void* x2
   //   dx1 = w1 u1,  dw1[r, l1] = sum over row r of <x1, u1> on degree l1
   // (likewise for x2), and with z = GTP(w1 x1, w2 x2)
   //   dwout[r, l] = sum over row r of <dy, z> on degree l.
+  if (n > 0 && p->L1 == p->L2 && p->L2 == p->Lout && p->L1 >= 1 && p->L1 <= 8 && !p->force_generic) {
+    // equal degrees 1..8: all gradients from one kernel, the products never
+    // in memory
+    gtp::WbwdArgs a{};
+    a.x1 = x1;
+    a.x2 = x2;
+    a.in_type = it;
+    a.dy = dy;
+    a.w1 = w1;
+    a.w2 = w2;
+    a.wo = wout;
+    a.dx1 = dx1;
+    a.dx2 = dx2;
+    a.dw1 = dw1;
+    a.dw2 = dw2;
+    a.dwo = dwout;
+    a.n = n;
+    a.C = C;
+    a.per_channel = per_channel;
+    a.need = (dwout ? 1 : 0) | (dx1 || dw1 ? 2 : 0) | (dx2 || dw2 ? 4 : 0) | (dw1 ? 16 : 0) | (dw2 ? 32 : 0);
+    a.waves = gtp::wbwd_waves(n, C, per_channel);
+    hipError_t e = hipSuccess;
+    if (dw1 || dw2 || dwout) {
+      const size_t bytes = size_t(gtp::wbwd_partial_floats(p->L1, a.waves, per_channel)) * sizeof(float);
+      e = hipMallocAsync(reinterpret_cast<void**>(&a.partial), bytes, st);
+      if (e != hipSuccess) return fail(GTP_ERR_ALLOC, std::string("hipMallocAsync: ") + hipGetErrorString(e));
+    }
+    bool done = false;
+    e = gtp::launch_wbwd_small(p->L1, a, st, &done);
+    const hipError_t ef = a.partial ? hipFreeAsync(a.partial, st) : hipSuccess;
+    if (done) {
+      if (e != hipSuccess) return hip_fail(e, "gtp_full_weighted_backward launch");
+      return ef == hipSuccess ? GTP_OK : hip_fail(ef, "hipFreeAsync");
+    }
+  }
   const int64_t nchunk = gtp::wgrad_nchunk(B, C, per_channel);
   const bool need_u1 = dx1 || dw1, need_u2 = dx2 || dw2;
   // workspace: u1 / u2 where dx1 / dx2 are not given, z, and the partials
