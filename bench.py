@@ -168,7 +168,9 @@ KERNEL_SOURCES = {
     "gtp_small.hip": ["gen_small_consts.cpp", "gtp_small.hpp", "gtp_small_core.hpp"],
     "gtp_escn.hip": ["gen_small_consts.cpp", "gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
     "gtp_wave.hip": ["gtp_fft.hpp"],
-    "gtp_mfma.hip": ["gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp"],
+    "gtp_mfma.hip": ["gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp", "gtp_split.hpp"],
+    "gtp_mixq.hip": ["gen_mixq_consts.cpp", "gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp", "gtp_mixq.hpp",
+                     "gtp_mixq_tables.cpp", "gtp_mixq_tables.hpp", "gtp_split.hpp"],
     "gtp_escn_wave.hip": ["gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
 }
 
@@ -213,8 +215,8 @@ def dominant_kernel(workload: str, L: int, escn: bool = False, conv: str = "auto
             return "k_conv_escn_wave", "mfma", "gtp_escn_wave.hip"
         return "k_escn_rot+k_conv_escn", "alu", "gtp_escn.hip"
     if workload == "mix":
-        # pair products (thread per product) and the mix on the matrix cores in one kernel
-        return "k_mix_fused", "alu", "gtp_small.hip"
+        # sampled channels, the weights' contraction and the analysis on the matrix cores in one kernel
+        return "k_mixq", "mfma", "gtp_mixq.hip"
     if workload in ("sweep", "highdeg", "edge16") and (L >= 16 or workload == "highdeg"):
         return ("k_full_wave4", "mfma", "gtp_wave.hip") if L > 32 else ("k_full_mfma", "mfma", "gtp_mfma.hip")
     if workload == "manybody":

@@ -20,9 +20,8 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libgtp.so")
 
-HIP_SOURCES = ["gtp_api.hip", "gtp_small.hip", "gtp_wave.hip", "gtp_mfma.hip", "gtp_generic.hip", "gtp_escn.hip", "gtp_escn_wave.hip",
-               "gtp_mix.hip",
-               "gtp_probe.hip", "gtp_wgrad.hip", "gtp_wbwd.hip"]
+HIP_SOURCES = ["gtp_api.hip", "gtp_small.hip", "gtp_wave.hip", "gtp_mfma.hip", "gtp_generic.hip", "gtp_escn.hip",
+               "gtp_escn_wave.hip", "gtp_mix.hip", "gtp_mixq.hip", "gtp_probe.hip", "gtp_wgrad.hip", "gtp_wbwd.hip"]
 CPP_SOURCES = ["gtp_tables.cpp", "gtp_escn_tables.cpp", "gtp_mfma_tables.cpp"]
 ARCH = "gfx950"
 # Packed fp32 VALU forms stay off: plain fp32 FMAs only.
@@ -39,29 +38,34 @@ def _hipcc() -> str:
 
 
 GEN = os.path.join(BUILD, "gen")
+# (generator, its other sources, outputs): the tables of the thread-per-product
+# kernels, and the operand images of the sample-domain channel mixing
+GENERATORS = [
+    ("gen_small_consts", ["gtp_tables.cpp", "gtp_escn_tables.cpp"], ["gtp_small_consts.inc", "gtp_escn_consts.inc"]),
+    ("gen_mixq_consts", ["gtp_tables.cpp", "gtp_mfma_tables.cpp", "gtp_mixq_tables.cpp"], ["gtp_mixq_consts.inc"]),
+]
 
 
 def generate_constants(verbose: bool = False) -> None:
-    """Compile and run the generator of the compile-time tables of the
-    thread-per-product kernels (from the library's own fp64 table builders)."""
+    """Compile and run the generators of the compile-time tables (from the
+    library's own fp64 table builders)."""
     os.makedirs(GEN, exist_ok=True)
-    exe = os.path.join(BUILD, "gen_small_consts")
-    cmd = ["g++", *CXX_FLAGS, "-o", exe, os.path.join(CSRC, "gen_small_consts.cpp"),
-           os.path.join(CSRC, "gtp_tables.cpp"), os.path.join(CSRC, "gtp_escn_tables.cpp")]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if verbose or r.returncode:
-        print(" ".join(cmd))
-        print(r.stdout, r.stderr)
-    if r.returncode:
-        raise RuntimeError("generator build failed")
-    out = os.path.join(GEN, "gtp_small_consts.inc")
-    out_e = os.path.join(GEN, "gtp_escn_consts.inc")
-    r = subprocess.run([exe, out + ".tmp", out_e + ".tmp"], capture_output=True, text=True)
-    if r.returncode:
-        print(r.stdout, r.stderr)
-        raise RuntimeError("generator failed")
-    os.replace(out + ".tmp", out)
-    os.replace(out_e + ".tmp", out_e)
+    for name, sources, outputs in GENERATORS:
+        exe = os.path.join(BUILD, name)
+        cmd = ["g++", *CXX_FLAGS, "-o", exe, *[os.path.join(CSRC, s) for s in (name + ".cpp", *sources)]]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        if verbose or r.returncode:
+            print(" ".join(cmd))
+            print(r.stdout, r.stderr)
+        if r.returncode:
+            raise RuntimeError("generator build failed")
+        outs = [os.path.join(GEN, o) for o in outputs]
+        r = subprocess.run([exe, *[o + ".tmp" for o in outs]], capture_output=True, text=True)
+        if r.returncode:
+            print(r.stdout, r.stderr)
+            raise RuntimeError("generator failed")
+        for o in outs:
+            os.replace(o + ".tmp", o)
 
 
 POISON_BUILD = os.path.join(ROOT, "_build_poison")
@@ -89,7 +93,8 @@ def build(verbose: bool = False, poison: bool = True) -> str:
     t0 = time.time()
     failed = []
     running = []
-    pending = sorted(jobs, key=lambda j: 0 if "gtp_small" in j[1] else 1 if "gtp_wbwd" in j[1] else 2)  # the longest first
+    slow = ("gtp_small", "gtp_mixq", "gtp_wbwd")  # the longest compilations first
+    pending = sorted(jobs, key=lambda j: next((i for i, n in enumerate(slow) if n in j[1]), len(slow)))
     while pending or running:
         while pending and len(running) < 8:
             cmd, obj, vi = pending.pop(0)

@@ -20,6 +20,7 @@
 #include "gtp_device.hpp"
 #include "gtp_escn.hpp"
 #include "gtp_mfma_tables.hpp"
+#include "gtp_mixq.hpp"
 #include "gtp_probe.hpp"
 #include "gtp_small.hpp"
 #include "gtp_tables.hpp"
@@ -555,18 +556,33 @@ gtp_status gtp_channel_mix(gtp_plan p, const void* x1, const void* x2, gtp_dtype
   const int nct = gtp::mix_fused_nct(int(Co));
   if (!p->force_generic && p->conv != GTP_CONV_DIRECT && nct > 0 && p->L1 == p->L2 && p->L2 == p->Lout &&
       p->L1 >= 1 && p->L1 <= 8 && B <= 0x7fffffff) {
-    // one kernel: the pair products of a batch entry stay on chip; only the
-    // weights in the kernel's blocked layout go through a workspace
+    // Equal degrees 1..8, one kernel per batch entry and only the weights in
+    // the kernel's layout in a workspace.  From kMixqPairs pairs in the sample
+    // domain (gtp_mixq.hip); below, the pair products themselves
+    // (k_mix_fused): there the sampled form's error against 64-bit results,
+    // 1.6e-7 to 2.1e-7 for any C1 C2, is the larger (pairs: 1.1e-7 at 16,
+    // 1.5e-7 to 1.8e-7 at 64, 2.2e-7 at 128, 5.8e-7 at 1024).
+    constexpr int64_t kMixqPairs = 128;
     int64_t nwb = 0;
     if (!mul_ok((P + 255) / 256 * 256, int64_t(16) * nct, &nwb) || nwb > INT64_MAX / 4)
       return fail(GTP_ERR_INVALID_ARG, "C1*C2 too large");
-    float* wb = nullptr;
-    e = hipMallocAsync(reinterpret_cast<void**>(&wb), size_t(nwb) * sizeof(float), st);
+    const bool mixq = P >= kMixqPairs && C1 * K <= 0x7fffffff && C2 * K <= 0x7fffffff && nwb <= INT64_MAX / 64;
+    // the matrix cores contract over the channels of one input; the cheaper of the two
+    const bool swap = mixq && gtp::mixq_steps(C2) * C1 < gtp::mixq_steps(C1) * C2;
+    gtp::MixqArgs a{swap ? x2 : x1, swap ? x1 : x2, it, W, swap ? 1 : C2, swap ? C2 : 1, nullptr, y, B,
+                    swap ? C2 : C1, swap ? C1 : C2, Co};
+    const size_t bytes = mixq ? size_t(gtp::mixq_work_bytes(Co, a.C1, a.C2)) : size_t(nwb) * sizeof(float);
+    e = hipMallocAsync(&a.work, bytes, st);
     if (e != hipSuccess) return fail(GTP_ERR_ALLOC, std::string("hipMallocAsync: ") + hipGetErrorString(e));
     bool done = false;
-    e = gtp::launch_mix_wt_blocks(W, wb, int(Co), P, nct, st);
-    if (e == hipSuccess) e = gtp::launch_mix_fused(p->dev, x1, x2, it, wb, y, B, C1, C2, int(Co), st, &done);
-    const hipError_t e2 = hipFreeAsync(wb, st);
+    if (mixq) {
+      e = gtp::launch_mixq(p->L1, a, st, &done);
+    } else {
+      float* const wb = static_cast<float*>(a.work);
+      e = gtp::launch_mix_wt_blocks(W, wb, int(Co), P, nct, st);
+      if (e == hipSuccess) e = gtp::launch_mix_fused(p->dev, x1, x2, it, wb, y, B, C1, C2, int(Co), st, &done);
+    }
+    const hipError_t e2 = hipFreeAsync(a.work, st);
     if (e != hipSuccess) return hip_fail(e, "gtp_channel_mix launch");
     if (e2 != hipSuccess) return hip_fail(e2, "hipFreeAsync");
     if (done) return GTP_OK;

@@ -1,0 +1,108 @@
+#include "gtp_mixq_tables.hpp"
+
+#include <cmath>
+
+#include "gtp_mfma_tables.hpp"
+#include "gtp_tables.hpp"
+
+namespace gtp {
+
+namespace {
+
+const double kPiQ = 3.14159265358979323846264338327950288;
+
+// Gauss-Legendre nodes and weights on [-1, 1] (Newton's method on P_n)
+void gauss_legendre(int n, std::vector<double>& x, std::vector<double>& w) {
+  x.assign(n, 0.0);
+  w.assign(n, 0.0);
+  for (int i = 0; i < n; ++i) {
+    double z = std::cos(kPiQ * (i + 0.75) / (n + 0.5)), d = 1.0;
+    for (int it = 0; it < 100; ++it) {
+      double p0 = 1.0, p1 = z;
+      for (int k = 2; k <= n; ++k) {
+        const double p2 = ((2 * k - 1) * z * p1 - (k - 1) * p0) / k;
+        p0 = p1;
+        p1 = p2;
+      }
+      if (n == 1) p0 = 1.0;
+      d = n * (z * p1 - p0) / (z * z - 1.0);
+      const double step = p1 / d;
+      z -= step;
+      if (std::fabs(step) < 1e-16) break;
+    }
+    x[i] = z;
+    w[i] = 2.0 / ((1.0 - z * z) * d * d);
+  }
+}
+
+template <int L>
+std::vector<uint16_t> images(int* ka) {
+  using G = MixqGeo<L>;
+  std::vector<double> z, w;
+  gauss_legendre(G::NTH, z, w);
+  std::vector<double> Y(size_t(G::Q) * G::K), wq(G::Q), th(ntri(L));
+  double amax = 0.0;
+  for (int a = 0; a < G::NTH; ++a) {
+    theta_factors(L, std::acos(z[a]), th.data());
+    for (int b = 0; b < G::NPH; ++b) {
+      const int q = a * G::NPH + b;
+      wq[q] = w[a] * 2.0 * kPiQ / G::NPH;
+      for (int l = 0; l <= L; ++l)
+        for (int m = -l; m <= l; ++m) {
+          const double ph = 2.0 * kPiQ * double((std::abs(m) * b) % G::NPH) / G::NPH;
+          const double v = th[tri(l, std::abs(m))] * (m < 0 ? std::sin(ph) : std::cos(ph));
+          Y[size_t(q) * G::K + l * l + l + m] = v;
+          amax = std::fmax(amax, std::fabs(wq[q] * v));
+        }
+    }
+  }
+  int ex = 0;
+  std::frexp(amax, &ex);
+  *ka = 4 - ex;  // largest entry in [2^3, 2^4)
+  auto part_of = [](double x, int part) {
+    const uint16_t h1 = half_bits(x);
+    return part == 0 ? h1 : half_bits(x - half_value(h1));
+  };
+  std::vector<uint16_t> v(G::HALVES, 0);
+  for (int lane = 0; lane < 64; ++lane) {
+    const int g = lane / 16, i = lane % 16;
+    for (int j = 0; j < 8; ++j)
+      for (int part = 0; part < 2; ++part) {
+        auto put = [&](int base, int frag, double x) {
+          v[size_t(base) + (size_t(frag * 2 + part) * 64 + lane) * 8 + j] = part_of(x, part);
+        };
+        for (int tile = 0; tile < G::NWQ * G::T; ++tile)
+          for (int s = 0; s < G::KS; ++s) {
+            const int q = 16 * tile + i, k = 32 * s + 8 * g + j;
+            put(G::YS, tile * G::KS + s, q < G::Q && k < G::K ? std::ldexp(Y[size_t(q) * G::K + k], kYs) : 0.0);
+          }
+        for (int kt = 0; kt < G::KT; ++kt)
+          for (int ws = 0; ws < G::NWQ * 4; ++ws) {
+            const int q = 16 * (G::T * (ws / 4) + j) + 4 * (ws % 4) + g, k = 16 * kt + i;
+            const bool in = j < G::T && q < G::Q && k < G::K;
+            put(G::YA, kt * G::NWQ * 4 + ws, in ? std::ldexp(wq[q] * Y[size_t(q) * G::K + k], *ka) : 0.0);
+          }
+      }
+  }
+  return v;
+}
+
+}  // namespace
+
+std::vector<uint16_t> build_mixq_images(int L, int* ka) {
+  switch (L) {
+    case 1: return images<1>(ka);
+    case 2: return images<2>(ka);
+    case 3: return images<3>(ka);
+    case 4: return images<4>(ka);
+    case 5: return images<5>(ka);
+    case 6: return images<6>(ka);
+    case 7: return images<7>(ka);
+    case 8: return images<8>(ka);
+    default: break;
+  }
+  *ka = 0;
+  return {};
+}
+
+}  // namespace gtp

@@ -1,0 +1,82 @@
+"""Channel mixing in the sample domain (equal degrees 1..8, C1 C2 >= 128, Co <=
+128): every degree, channel counts about the 16 and 32 of the operand tiles, in
+both roles of the two inputs, output channels about the 16 and 32 of a
+workgroup, batches that leave the last workgroup of the low degrees short.
+
+Tolerances.  Per output row |y - y64| <= 1e-5 sum_p |W_p| |T_p| (the other mix
+tests' bound on the terms): the split operands keep 2^-22 of the factors, the
+contractions round at 2^-24 of partial sums."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gtp_oracle as O  # noqa: E402
+from paper_2401_10216_amd import gtp  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _products(L, x1, x2):
+    B, C1, K = x1.shape
+    C2 = x2.shape[1]
+    a = np.repeat(x1[:, :, None], C2, 2).reshape(-1, K)
+    b = np.repeat(x2[:, None], C1, 1).reshape(-1, K)
+    return O.gtp(a, b, L, L, L).reshape(B, C1 * C2, K)
+
+
+def _check(L, x1, x2, W, tol=1e-5):
+    """Row by row against the oracle's pair products, in units of the terms."""
+    y = gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1.cuda(), x2.cuda(), W.cuda())
+    T = _products(L, x1.double().numpy(), x2.double().numpy())
+    w = W.double().numpy().reshape(W.shape[0], -1)
+    ref = np.einsum("op,bpk->bok", w, T)
+    bound = np.einsum("op,bp->bo", np.abs(w), np.linalg.norm(T, axis=2))
+    err = np.linalg.norm(y.cpu().numpy().astype(np.float64) - ref, axis=2)
+    assert (err <= tol * bound).all(), (L, (err / np.maximum(bound, 1e-300)).max())
+
+
+@pytest.mark.parametrize("L", range(1, 9))
+@pytest.mark.parametrize("B,C1,C2,Co,dt", [(1, 2, 64, 1, torch.float32), (5, 16, 8, 16, torch.float32),
+                                           (3, 17, 33, 17, torch.bfloat16), (2, 33, 4, 33, torch.float32),
+                                           (5, 40, 65, 2, torch.float32), (2, 12, 11, 128, torch.bfloat16)])
+def test_sizes(L, B, C1, C2, Co, dt):
+    g = torch.Generator().manual_seed(1000 * L + C1)
+    x1, x2 = (torch.randn((B, c, (L + 1) ** 2), generator=g).to(dt) for c in (C1, C2))
+    _check(L, x1, x2, torch.randn((Co, C1, C2), generator=g))
+
+
+@pytest.mark.parametrize("L", [1, 4, 6, 8])
+def test_channel_scales(L):
+    """Channels over many orders of magnitude, every output weighing one pair:
+    each row holds to its own size, in either input's role."""
+    g = torch.Generator().manual_seed(L)
+    n = 20
+    x1, x2 = (torch.randn((3, n, (L + 1) ** 2), generator=g) for _ in range(2))
+    x1 = x1 * torch.logspace(-12, 6, n)[None, :, None]
+    x2 = x2 * torch.logspace(8, -9, n)[None, :, None]
+    W = torch.zeros((n, n, n))
+    for i in range(n):
+        W[i, i, i] = 10.0 ** (i - 8)
+    _check(L, x1, x2, W)
+    _check(L, x2, x1, W)
+    x1[1] = 0.0  # an entry of zeros, and a channel of zeros
+    x2[2, 5] = 0.0
+    _check(L, x1, x2, W)
+
+
+@pytest.mark.parametrize("L", [1, 2, 6])
+def test_not_finite_stays_in_its_entry(L):
+    g = torch.Generator().manual_seed(L)
+    x1, x2 = (torch.randn((6, 16, (L + 1) ** 2), generator=g).cuda() for _ in range(2))
+    W = torch.randn((4, 16, 16), generator=g).cuda()
+    plan = gtp.Plan(L, L, L)
+    want = gtp.gtp_channel_mix(plan, x1, x2, W)
+    x1[1, 3, 0] = float("nan")
+    x2[4, 15, 1] = float("inf")
+    got = gtp.gtp_channel_mix(plan, x1, x2, W)
+    for b in range(6):
+        if b in (1, 4):
+            assert not torch.isfinite(got[b]).any(), b
+        else:
+            assert torch.equal(got[b], want[b]), b
