@@ -1004,6 +1004,7 @@ gtp_status gtp_selfproduct(int L, int nu, int Lout, unsigned mode, const void* x
     if ((s = cached_plan(L, L, Lout, 0u, &p)) != GTP_OK) return s;
     bool done = false;
     e = gtp::launch_full_small(p->dev, x, it, x, it, n, y, 0, kNoWeights, st, &done);
+    if (!done) e = gtp::launch_self_stepwise_small(p->dev, p->dev, nu, x, it, n, y, st, &done);  // its first product
     if (!done) e = gtp::launch_full_generic(p->dev, x, it, x, it, n, y, 0, kNoWeights, st);
     return e == hipSuccess ? GTP_OK : hip_fail(e, "gtp_selfproduct launch");
   }

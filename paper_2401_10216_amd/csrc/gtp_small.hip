@@ -455,13 +455,23 @@ hipError_t launch_chain(const DevTables& t1, const DevTables& t2, int nu, const 
 
 }  // namespace
 
-// (L1, L2, Lout) pair products and (L, nu, Lout) fused powers with a
-// thread-per-product instantiation.  Everything else takes the generic path.
+// (L1, L2, Lout) pair products, (L, nu, Lout) fused powers and (L, Lout) chains
+// with a thread-per-product instantiation.  Everything else takes the generic
+// path.  Powers and chains: every L and Lout in 1..3 (powers: nu in 2..4, the
+// chain's nu is a loop), the degrees of the many-body features they are for.
+// One launch of a lane per product against the generic kernel's workgroup per
+// product (and per step of a chain, through a workspace), 64000 products fp32:
+// chains of L = 3, nu = 2 / 3 / 4 to Lout = 2 574 / 1134 / 1687 -> 14 / 16 / 15
+// us (launch-bound), fourth power of L = 3 to Lout = 3 583 -> 14 us; errors
+// against 64-bit results 0.75 to 1.0 of the generic kernel's, 1.03 at the
+// fourth power of L = 1 (the order of the fp32 sums).
 #define GTP_SMALL_PAIRS(X) \
   X(1, 1, 1) X(2, 2, 2) X(3, 3, 3) X(4, 4, 4) X(5, 5, 5) X(6, 6, 6) X(7, 7, 7) X(8, 8, 8) X(2, 2, 3) X(3, 2, 3) X(1, 2, 2) \
       X(2, 1, 3)
-#define GTP_SMALL_POWERS(X) X(2, 2, 3) X(2, 3, 3) X(2, 4, 3) X(1, 3, 2) X(3, 3, 3)
-#define GTP_SMALL_CHAINS(X) X(2, 3) X(1, 2) X(3, 3) X(2, 2)
+#define GTP_SMALL_POWERS_OF(X, a) \
+  X(a, 2, 1) X(a, 2, 2) X(a, 2, 3) X(a, 3, 1) X(a, 3, 2) X(a, 3, 3) X(a, 4, 1) X(a, 4, 2) X(a, 4, 3)
+#define GTP_SMALL_POWERS(X) GTP_SMALL_POWERS_OF(X, 1) GTP_SMALL_POWERS_OF(X, 2) GTP_SMALL_POWERS_OF(X, 3)
+#define GTP_SMALL_CHAINS(X) X(1, 1) X(1, 2) X(1, 3) X(2, 1) X(2, 2) X(2, 3) X(3, 1) X(3, 2) X(3, 3)
 
 hipError_t launch_full_small(const DevTables& t, const void* x1, int it1, const void* x2, int it2, int64_t n,
                              float* y, int nu, const DegWeights& wt, hipStream_t s, bool* supported) {
@@ -614,7 +624,7 @@ hipError_t launch_self_stepwise_small(const DevTables& t1, const DevTables& t2, 
                                       int64_t n, float* y, hipStream_t s, bool* supported) {
   *supported = true;
 #define GTP_CASE(a, c) \
-  if (t1.L1 == a && t1.L2 == a && t1.Lout == c && t2.L1 == c && t2.L2 == a && t2.Lout == c) \
+  if (t1.L1 == a && t1.L2 == a && t1.Lout == c && (nu == 2 || (t2.L1 == c && t2.L2 == a && t2.Lout == c))) \
     return launch_chain<a, c>(t1, t2, nu, x, in_type, n, y, s);
   GTP_SMALL_CHAINS(GTP_CASE)
 #undef GTP_CASE

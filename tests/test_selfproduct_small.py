@@ -1,0 +1,36 @@
+"""Many-body products on the thread-per-product kernels: every (L, nu, Lout)
+they are instantiated for, L = 1..3, nu = 2..4, Lout = 1..3, both modes and
+input types, about the 64 products of a workgroup.
+
+Tolerance: 1e-5 of a row's scale, that of the other fp32 product tests; each of
+the up to three products of a chain adds about 3e-7 of its terms.  Where a
+row's terms cancel its scale is theirs, |x|^nu (4 pi)^(-(nu - 1) / 2), the
+product of the norms times the l = 0 Gaunt coefficient of each product."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import gtp_oracle as O  # noqa: E402
+from paper_2401_10216_amd import gtp  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+MODES = {"stepwise": gtp.GTP_SELF_STEPWISE, "fused": gtp.GTP_SELF_FUSED}
+
+
+@pytest.mark.parametrize("mode", ["stepwise", "fused"])
+@pytest.mark.parametrize("L", [1, 2, 3])
+@pytest.mark.parametrize("nu", [2, 3, 4])
+@pytest.mark.parametrize("Lout", [1, 2, 3])
+def test_every_instantiation(L, nu, Lout, mode):
+    for n, dt in ((1, torch.float32), (65, torch.float32), (130, torch.bfloat16)):
+        g = torch.Generator().manual_seed(100 * L + 10 * nu + Lout)
+        deg = torch.tensor([l for l in range(L + 1) for _ in range(2 * l + 1)])
+        x = (torch.randn((n, 1, (L + 1) ** 2), generator=g) / torch.sqrt(2.0 * deg + 1)).to(dt)
+        y = gtp.gtp_selfproduct(x.cuda(), L, nu, Lout, MODES[mode]).cpu().numpy().reshape(n, -1)
+        xd = x.double().numpy().reshape(n, -1)
+        ref = O.selfproduct(xd, L, nu, Lout, mode)
+        terms = np.linalg.norm(xd, axis=1) ** nu * (4 * np.pi) ** (-(nu - 1) / 2)
+        err = np.abs(y - ref).max(axis=1)
+        assert (err <= 1e-5 * np.maximum(np.linalg.norm(ref, axis=1), terms)).all(), (n, dt)
