@@ -12,6 +12,7 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
 import time
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -93,15 +94,23 @@ def build(verbose: bool = False, poison: bool = True) -> str:
     t0 = time.time()
     failed = []
     running = []
-    slow = ("gtp_small", "gtp_mixq", "gtp_wbwd")  # the longest compilations first
+    slow = ("gtp_mixq", "gtp_small", "gtp_escn.", "gtp_wbwd")  # the longest compilations first
     pending = sorted(jobs, key=lambda j: next((i for i, n in enumerate(slow) if n in j[1]), len(slow)))
     while pending or running:
         while pending and len(running) < 8:
             cmd, obj, vi = pending.pop(0)
-            running.append((subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True), cmd,
-                            obj))
-        p, cmd, obj = running.pop(0)
-        out, _ = p.communicate()
+            log = tempfile.TemporaryFile("w+")
+            running.append((subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT), cmd, obj, log))
+        # whichever ends first (a compiler's output goes to a file: nothing waits on a pipe)
+        done = next((r for r in running if r[0].poll() is not None), None)
+        if done is None:
+            time.sleep(0.05)
+            continue
+        running.remove(done)
+        p, cmd, obj, log = done
+        log.seek(0)
+        out = log.read()
+        log.close()
         if verbose or p.returncode:
             print(" ".join(cmd))
             if out:
