@@ -11,8 +11,8 @@
 //
 // All contractions run on v_mfma_f32_16x16x32_f16 with split operands (the
 // part-2 x part-2 products, 2^-22 of a term, left out); the accumulators, F2
-// and the sum over c2 are fp32.  Powers of two bring every input channel and
-// every output channel's weights into the half type's range.  In the sum over
+// and the sum over c2 are fp32.  Powers of two bring every input channel, every
+// output channel's weights and its sampled sums into the half type's range.  In the sum over
 // c1 the channels' own scales must stand: channels whose scales lie within
 // 2^kClass of the largest enter together, at that one's scale; smaller ones,
 // if a batch entry has such, in further turns at theirs (one output channel
@@ -135,12 +135,12 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
   // a wave's own LDS: 32 staged rows, then F2's columns, then its sampled sums
   constexpr int REG = (32 * S > 32 * 16 * U ? 32 * S : 32 * 16 * U);
   static_assert(REG * 4 >= 8192 && T <= 8, "the sampled sums of a 16-row tile in the wave's region");
-  __shared__ __align__(16) float lds[NWQ * REG + NWQ * 4];
-  lds_poison(lds, NWQ * REG + NWQ * 4);
+  __shared__ __align__(16) float lds[NWQ * REG + NWQ * 16];
+  lds_poison(lds, NWQ * REG + NWQ * 16);
   const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* const st = lds + wave * REG;
-  float* const mxb = lds + NWQ * REG;  // one maximum per wave
+  float* const mxb = lds + NWQ * REG;  // the output rows' maxima per wave
   const int64_t b0 = int64_t(blockIdx.x) * NB;
   const int64_t nc1 = (C1 + CK - 1) / CK;
 
@@ -446,18 +446,30 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     cfor<0, NCOT>([&](auto CC) {
       constexpr int b = decltype(BB)::value, cc = decltype(CC)::value;
       const int64_t co0 = 16 * (ct0 + cc);
-      float mx = 0.0f;
-      cfor<0, T>([&](auto TT) {
-        constexpr int u = b * T + decltype(TT)::value;
-        cfor<0, 4>([&](auto R) { mx = fmaxf(mx, finite_abs(acc[u][cc][decltype(R)::value])); });
+      // an exponent for each output row: one output channel's sums may lie any
+      // way below another's
+      int eg[4];
+      cfor<0, 4>([&](auto R) {
+        constexpr int r = decltype(R)::value;
+        float mx = 0.0f;
+        cfor<0, T>([&](auto TT) { mx = fmaxf(mx, finite_abs(acc[b * T + decltype(TT)::value][cc][r])); });
+#pragma unroll
+        for (int d = 1; d < 16; d *= 2) mx = fmaxf(mx, __shfl_xor(mx, d));
+        if constexpr (NWQ > 1) {
+          if (i == 0) mxb[wave * 16 + 4 * g + r] = mx;
+        } else {
+          eg[r] = exponent_of(mx);
+        }
       });
-      mx = wave_max(mx);
       if constexpr (NWQ > 1) {
-        if (lane == 0) mxb[wave] = mx;
         __syncthreads();
-        cfor<0, NWQ>([&](auto W) { mx = fmaxf(mx, mxb[decltype(W)::value]); });
+        cfor<0, 4>([&](auto R) {
+          constexpr int r = decltype(R)::value;
+          float mx = 0.0f;
+          cfor<0, NWQ>([&](auto W) { mx = fmaxf(mx, mxb[decltype(W)::value * 16 + 4 * g + r]); });
+          eg[r] = exponent_of(mx);
+        });
       }
-      const int eg = exponent_of(mx);
       // parts 1, then 2: [row][point of the tile][tile]
       u4* const gs = reinterpret_cast<u4*>(st);
       cfor<0, 4>([&](auto R) {
@@ -465,7 +477,7 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
         float v[8];
         cfor<0, 8>([&](auto TT) {
           constexpr int t = decltype(TT)::value;
-          v[t] = t < T ? ldexpf(acc[b * T + (t < T ? t : 0)][cc][r], kGs - eg) : 0.0f;
+          v[t] = t < T ? ldexpf(acc[b * T + (t < T ? t : 0)][cc][r], kGs - eg[r]) : 0.0f;
         });
         const u4 p = split4(v[0], v[1], v[2], v[3]), q = split4(v[4], v[5], v[6], v[7]);
         gs[(4 * g + r) * 16 + i] = u4{p[0], p[1], q[0], q[1]};
@@ -495,11 +507,11 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
           if constexpr (w > 0) hi[0][0] += hi[w][0];
         });
         d += hi[0][0];
-        const int k = 16 * kt + i, ex = e1[b] + e2[b] + eg - kGs - ka;
+        const int k = 16 * kt + i, ex = e1[b] + e2[b] - kGs - ka;
         cfor<0, 4>([&](auto R) {
           constexpr int r = decltype(R)::value;
           const int64_t co = co0 + 4 * g + r;
-          if (b0 + b < B && co < Co && k < K) y[((b0 + b) * Co + co) * K + k] = ldexpf(d[r], ex + ew[co]);
+          if (b0 + b < B && co < Co && k < K) y[((b0 + b) * Co + co) * K + k] = ldexpf(d[r], ex + eg[r] + ew[co]);
         });
       }
       __syncthreads();  // the regions are read: the next rows, or stage, may land there

@@ -65,6 +65,32 @@ def test_channel_scales(L):
     _check(L, x1, x2, W)
 
 
+def _roles(x1, x2, W):
+    """The call, and the same with the two inputs' roles exchanged."""
+    return (x1, x2, W), (x2, x1, W.transpose(1, 2).contiguous())
+
+
+@pytest.mark.parametrize("L", [1, 2, 4, 6, 8])
+@pytest.mark.parametrize("n", [16, 33])
+@pytest.mark.parametrize("s", [1e-6, 1e-12, 1e-30])
+def test_outputs_of_any_size(L, n, s):
+    """Half of one input's channels s times smaller, each output weighing one
+    of them (all of the other input's): outputs of one tile lie s apart, and
+    each holds to its own terms.
+
+    Tolerance: the factors stand for their values within 2^-22, the sums round
+    at 2^-24 of partial sums; together below 5 times 2^-22 = 1.2e-6 of the
+    terms, 2e-6 allowed (the fp32 pair products show 1.5e-7)."""
+    g = torch.Generator().manual_seed(L)
+    x1, x2 = (torch.randn((3, n, (L + 1) ** 2), generator=g) for _ in range(2))
+    x1[:, n // 2:] *= s
+    W = torch.zeros((n, n, n))
+    for i in range(n):
+        W[i, i] = torch.randn(n, generator=g)
+    for call in _roles(x1, x2, W):
+        _check(L, *call, tol=2e-6)
+
+
 @pytest.mark.parametrize("L", [1, 2, 6])
 def test_not_finite_stays_in_its_entry(L):
     g = torch.Generator().manual_seed(L)
