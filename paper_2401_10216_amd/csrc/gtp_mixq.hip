@@ -64,6 +64,8 @@ constexpr int kWs = 12;     // weights below 2^kWs
 constexpr int kGs = 13;     // sampled sums below 2^kGs
 constexpr int kClass = 10;  // scales of one turn: samples below 2^14, the smallest channels' near 1
 constexpr int kNone = -140; // the exponent of zeros
+constexpr int kBad = 1 << 20;     // of a channel with a NaN or Inf: in every turn
+constexpr int kDone = -(1 << 20); // the turn of an entry that has had all its channels
 
 __device__ __forceinline__ float finite_abs(float v) {
   const float a = fabsf(v);
@@ -197,15 +199,21 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     }
     // the rows' exponents: 64 / NR lanes to a row
     float mx = 0.0f;
+    int bad = 0;
     cfor<0, (K + 64 / NR - 1) / (64 / NR)>([&](auto J) {
       const int k = lane / NR + 64 / NR * decltype(J)::value;
-      mx = fmaxf(mx, finite_abs(st[(lane % NR) * S + (k < K ? k : 0)]));
+      const float w = st[(lane % NR) * S + (k < K ? k : 0)];
+      mx = fmaxf(mx, finite_abs(w));
+      bad |= !(fabsf(w) < __builtin_inff());
     });
 #pragma unroll
-    for (int d = NR; d < 64; d *= 2) mx = fmaxf(mx, __shfl_xor(mx, d));
-    const int er = exponent_of(mx);
+    for (int d = NR; d < 64; d *= 2) {
+      mx = fmaxf(mx, __shfl_xor(mx, d));
+      bad |= __shfl_xor(bad, d);
+    }
+    const int er = bad ? kBad : exponent_of(mx);
     if (C <= NR) {
-      int em = er;
+      int em = bad ? kNone : er;
 #pragma unroll
       for (int d = 1; d < NR; d *= 2) {
         const int o = __shfl_xor(em, d);
@@ -222,7 +230,7 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     });
     u4 a[RT][KS][2];
     cfor<0, RT>([&](auto RR) {
-      const int ea = kXs - __shfl(er, 16 * decltype(RR)::value + i);
+      const int es = __shfl(er, 16 * decltype(RR)::value + i), ea = kXs - (es == kBad ? 0 : es);
       cfor<0, KS>([&](auto SS) {
         constexpr int rt = decltype(RR)::value, s = decltype(SS)::value;
         float v[8];
@@ -311,7 +319,8 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
           cfor<0, 4>([&](auto R) {
             constexpr int r = decltype(R)::value;
             const int rel = e[r] - ec[b];
-            d[r] = rel <= 0 && rel > -kClass ? ldexpf(d[r], rel) : 0.0f;
+            // (a NaN or Inf reaches every sample of its channel, and stands)
+            if (e[r] != kBad) d[r] = rel <= 0 && rel > -kClass ? ldexpf(d[r], rel) : 0.0f;
             if constexpr (t == 0) {
               if (rel <= -kClass) under = e[r] > under ? e[r] : under;
             }
@@ -438,7 +447,7 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     cfor<0, NB>([&](auto BB) {
       constexpr int b = decltype(BB)::value;
       more = more || below[b] > kNone;
-      ec[b] = below[b];
+      ec[b] = below[b] > kNone ? below[b] : kDone;
     });
   }
   // ---- analysis, one batch entry and 16 output channels at a time

@@ -106,3 +106,26 @@ def test_not_finite_stays_in_its_entry(L):
             assert not torch.isfinite(got[b]).any(), b
         else:
             assert torch.equal(got[b], want[b]), b
+
+
+@pytest.mark.parametrize("L", [1, 2, 6])
+@pytest.mark.parametrize("C1,C2", [(16, 8), (8, 16), (40, 33), (33, 40)])
+@pytest.mark.parametrize("which", [0, 1])
+def test_channels_without_a_finite_value(L, C1, C2, which):
+    """A channel of NaN, and one of a single Inf among zeros, beside ordinary
+    ones, in either input and either role, one and several tiles of channels:
+    none of the entry's outputs is a number, the other entries' are unchanged."""
+    g = torch.Generator().manual_seed(L)
+    x = [torch.randn((6, c, (L + 1) ** 2), generator=g).cuda() for c in (C1, C2)]
+    W = torch.randn((4, C1, C2), generator=g).cuda()
+    plan = gtp.Plan(L, L, L)
+    want = gtp.gtp_channel_mix(plan, *x, W)
+    x[which][1, 3] = float("nan")
+    x[which][4, 5] = 0.0
+    x[which][4, 5, 0] = float("inf")
+    got = gtp.gtp_channel_mix(plan, *x, W)
+    for b in range(6):
+        if b in (1, 4):
+            assert not torch.isfinite(got[b]).any(), b
+        else:
+            assert torch.equal(got[b], want[b]), b
