@@ -169,8 +169,8 @@ KERNEL_SOURCES = {
     "gtp_escn.hip": ["gen_small_consts.cpp", "gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
     "gtp_wave.hip": ["gtp_fft.hpp"],
     "gtp_mfma.hip": ["gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp", "gtp_split.hpp"],
-    "gtp_mixq.hip": ["gen_mixq_consts.cpp", "gtp_mfma_tables.cpp", "gtp_mfma_tables.hpp", "gtp_mixq.hpp",
-                     "gtp_mixq_tables.cpp", "gtp_mixq_tables.hpp", "gtp_split.hpp"],
+    "gtp_mixq.hip": ["gen_mixq_consts.cpp", "gtp_mixq.hpp", "gtp_mixq_tables.cpp", "gtp_mixq_tables.hpp",
+                     "gtp_split.hpp"],
     "gtp_escn_wave.hip": ["gtp_escn.hpp", "gtp_escn_tables.cpp", "gtp_escn_tables.hpp"],
 }
 

@@ -43,7 +43,7 @@ GEN = os.path.join(BUILD, "gen")
 # kernels, and the operand images of the sample-domain channel mixing
 GENERATORS = [
     ("gen_small_consts", ["gtp_tables.cpp", "gtp_escn_tables.cpp"], ["gtp_small_consts.inc", "gtp_escn_consts.inc"]),
-    ("gen_mixq_consts", ["gtp_tables.cpp", "gtp_mfma_tables.cpp", "gtp_mixq_tables.cpp"], ["gtp_mixq_consts.inc"]),
+    ("gen_mixq_consts", ["gtp_tables.cpp", "gtp_mixq_tables.cpp"], ["gtp_mixq_consts.inc"]),
 ]
 
 

@@ -17,16 +17,15 @@ int main(int argc, char** argv) {
   }
   std::fprintf(f, "// generated from gtp_mixq_tables.cpp\ntemplate <int L> struct MixqImages;\n");
   for (int L = 1; L <= 8; ++L) {
-    int ka = 0;
-    const std::vector<uint16_t> v = gtp::build_mixq_images(L, &ka);
+    const std::vector<uint16_t> v = gtp::build_mixq_images(L);
     std::fprintf(f, "__device__ const uint32_t kMixqImages%d[%zu] __attribute__((aligned(16))) = {", L, v.size() / 2);
     for (size_t i = 0; i < v.size(); i += 2)
       std::fprintf(f, "%s%uu,", i % 24 ? "" : "\n", unsigned(v[i]) | unsigned(v[i + 1]) << 16);
     std::fprintf(f, "\n};\n");
     std::fprintf(f,
-                 "template <> struct MixqImages<%d> {\n  static constexpr int ka = %d;\n"
+                 "template <> struct MixqImages<%d> {\n"
                  "  static __device__ const uint32_t* get() { return kMixqImages%d; }\n};\n",
-                 L, ka, L);
+                 L, L);
   }
   if (std::fclose(f) != 0) {
     std::perror(argv[1]);

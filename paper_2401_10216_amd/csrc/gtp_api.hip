@@ -558,10 +558,10 @@ gtp_status gtp_channel_mix(gtp_plan p, const void* x1, const void* x2, gtp_dtype
       p->L1 >= 1 && p->L1 <= 8 && B <= 0x7fffffff) {
     // Equal degrees 1..8, one kernel per batch entry and only the weights in
     // the kernel's layout in a workspace.  From kMixqPairs pairs in the sample
-    // domain (gtp_mixq.hip); below, the pair products themselves
-    // (k_mix_fused): there the sampled form's error against 64-bit results,
-    // 1.6e-7 to 2.1e-7 for any C1 C2, is the larger (pairs: 1.1e-7 at 16,
-    // 1.5e-7 to 1.8e-7 at 64, 2.2e-7 at 128, 5.8e-7 at 1024).
+    // domain (gtp_mixq.hip: error against 64-bit results 7.5e-8 to 1.0e-7 at 128
+    // pairs, 1.0e-7 to 1.2e-7 at 1024); below, the pair products themselves
+    // (k_mix_fused: 1.1e-7 at 16, 1.5e-7 to 1.8e-7 at 64, 2.2e-7 at 128, 5.8e-7
+    // at 1024).
     constexpr int64_t kMixqPairs = 128;
     int64_t nwb = 0;
     if (!mul_ok((P + 255) / 256 * 256, int64_t(16) * nct, &nwb) || nwb > INT64_MAX / 4)

@@ -9,30 +9,33 @@
 // every point (rows co, contraction index c1, columns the points), and the sum
 // over c2 one multiply-add per point on its result.
 //
-// All contractions run on v_mfma_f32_16x16x32_f16 with split operands (the
-// part-2 x part-2 products, 2^-22 of a term, left out); the accumulators, F2
-// and the sum over c2 are fp32.  Powers of two bring every input channel, every
-// output channel's weights and its sampled sums into the half type's range.  In the sum over
-// c1 the channels' own scales must stand: channels whose scales lie within
-// 2^kClass of the largest enter together, at that one's scale; smaller ones,
-// if a batch entry has such, in further turns at theirs (one output channel
-// may weigh only them).  The accumulator layout of the sampling (rows =
-// channels) is the operand layout of the contraction over c1, so F1 stays in
-// registers; F2 goes through the wave's own LDS columns, and the sampled sums
-// through LDS to the analysis.
+// All contractions run on v_mfma_f32_16x16x32_bf16 with operands in three bf16
+// parts (gtp_split.hpp), which hold fp32 values exactly and, unlike fp16 parts,
+// whatever the sizes of the values beside them: a channel, weight or output far
+// below its neighbours keeps its bits.  Six products of parts stand for one (b2
+// x b3 and b3 x b3, 2^-24 of a term at worst, are left out; three products
+// where the inputs are bf16); the accumulators, F2 and the sum over c2 are fp32.
+// One power of two per batch entry and input, and per output channel's
+// weights, keeps products of large and small factors within fp32's exponents:
+// inputs below 2^kX1 and 2^kX2, weights below 2^kW.  That leaves a channel its
+// bits down to 2^-148 (3e-45) of the largest value of its entry, a weight down
+// to 2^-110 (8e-34) of its output channel's largest.  The accumulator layout of the sampling (rows = channels) is the operand layout of
+// the contraction over c1, so F1 stays in registers; F2 goes through the wave's
+// own LDS columns, and the sampled sums through LDS to the analysis.
 //
 // Bound: issue of the matrix instructions (L = 6, C1 = C2 = Co = 32, per wave
-// and batch entry: 1152 over c1, 144 for the sampling, 96 for the analysis, 16
+// and batch entry: 2304 over c1, 288 for the sampling, 192 for the analysis, 16
 // cycles each) and of the vector instructions beside them, mostly the
 // multiply-adds over c2 and the splits; the two do not overlap on a SIMD.
 // Waves of their own columns rather than of their own channels: F1, F2 and the
 // sums then never leave the wave until the analysis.  Loads go out together
-// (staged rows, tiles of the quadrature's values, weights channels ahead):
-// with one load per wait the kernel took 652 us instead of 386 (B = 8192).
-// There 1.05 ms -> 0.40 ms against the pair products (k_mix_fused), error
-// against 64-bit results 5.8e-7 -> 1.7e-7; L = 8, 600 entries of 64 x 64 -> 64
-// channels 1.94 -> 0.42 ms; L = 1, 500 of those 151 -> 93 us; C1 C2 = 128 at
-// L <= 4 the same as before.
+// (staged rows, tiles of the quadrature's values, weights channels ahead).
+// Measured, L = 6, 8192 entries of 32 x 32 -> 32: 526 us, against 1018 us of the
+// pair products (k_mix_fused), error against 64-bit results 1.1e-7 against
+// 5.8e-7 (7.5e-8 to 1.9e-7 against 2.2e-7 to 1.2e-6 over degrees 1..8, 128 to 4096
+// pairs).  With operands in two fp16 parts, three products and scales shared by
+// the channels of a turn, by a row of weights and by an output row, 352 us, but a
+// weight 1e-6 of its row's largest kept 17 bits and one 1e-12 of it none.
 #include "gtp_ct.hpp"
 #include "gtp_device.hpp"
 #include "gtp_mixq.hpp"
@@ -59,31 +62,46 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int d = 1; d < 64; d *= 2) v = fmaxf(v, __shfl_xor(v, d));
   return v;
 }
-constexpr int kXs = 6;      // input channels below 2^kXs
-constexpr int kWs = 12;     // weights below 2^kWs
-constexpr int kGs = 13;     // sampled sums below 2^kGs
-constexpr int kClass = 10;  // scales of one turn: samples below 2^14, the smallest channels' near 1
-constexpr int kNone = -140; // the exponent of zeros
-constexpr int kBad = 1 << 20;     // of a channel with a NaN or Inf: in every turn
-constexpr int kDone = -(1 << 20); // the turn of an entry that has had all its channels
+// Exponents of the scaled inputs and weights.  A sample is below 2^5 of its
+// channel's largest coefficient (degrees <= 8), the analysis adds 2^5: outputs
+// stay below 2^(kX1 + kW + kX2 + 15) C1 C2 < 2^127 (C1 C2 < 2^36: the weights
+// fit the memory).
+constexpr int kX1 = 38, kW = 0, kX2 = 38;
 
-__device__ __forceinline__ float finite_abs(float v) {
-  const float a = fabsf(v);
-  return a < __builtin_inff() ? a : 0.0f;  // NaN and Inf set no scale
+// e with v < 2^e (0 for v = 0; of no consequence for Inf, whose channel and
+// outputs are NaN)
+__device__ __forceinline__ int exponent_of(float v) { return __builtin_amdgcn_frexp_expf(v); }
+
+// The wave's LDS writes before, its reads after (or the other way round): one
+// lane reads what another wrote.  The hardware keeps a wave's LDS accesses in
+// order; this keeps the compiler from moving them.
+__device__ __forceinline__ void lds_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
-// e with v < 2^e, at least kNone (so for v = 0)
-__device__ __forceinline__ int exponent_of(float v) {
-  const int e = v > 0.0f ? __builtin_amdgcn_frexp_expf(v) : kNone;
-  return e < kNone ? kNone : e;
+
+// f(part of one operand, part of the other) for the six products of parts that
+// count, the smallest first.
+template <typename F>
+__device__ __forceinline__ void each_pair(F&& f) {
+  using P1 = std::integral_constant<int, 0>;
+  using P2 = std::integral_constant<int, 1>;
+  using P3 = std::integral_constant<int, 2>;
+  f(P3{}, P1{});
+  f(P2{}, P2{});
+  f(P1{}, P3{});
+  f(P2{}, P1{});
+  f(P1{}, P2{});
+  f(P1{}, P1{});
 }
 
 // The weights' operand images: for every 16-row tile of co, chunk of CK c1's
-// and c2, lane 16 g + i holds row co = 16 tile + i, contraction indices c1 = 16
-// (j / 4) + 4 g + j % 4 of the chunk (CK = 32) or 4 g + j % 4 twice (CK = 16),
-// part 1 then part 2, W times 2^(kWs - ew[co]), ew[co] the exponent of that
-// output channel's weights.  s1, s2: strides of c1 and c2 in W.  One
-// workgroup per tile (y) and share of the c2's (x); each takes its tile's
-// exponents from the rows themselves.
+// and c2, lane 16 g + i holds row co = 16 tile + i, three operands: CK = 32:
+// parts 1, 2, 3 of c1 = 16 (j / 4) + 4 g + j % 4 of the chunk, j < 8; CK = 16:
+// of c1 = 4 g + j, j < 4, parts (1, 1), (2, 2), (1, 3); W times 2^(kW - ew[co]),
+// ew[co] the exponent of that output channel's weights.  s1, s2: strides of c1
+// and c2 in W.  One workgroup per tile (y) and share of the c2's (x); each takes
+// its tile's exponents from the rows themselves.
 template <int CK>
 __global__ __launch_bounds__(1024) void k_mixq_weights(const float* __restrict__ W, u4* __restrict__ img,
                                                        int* __restrict__ ew, int64_t Co, int64_t C1, int64_t C2,
@@ -101,7 +119,7 @@ __global__ __launch_bounds__(1024) void k_mixq_weights(const float* __restrict__
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = row[e0 + 64 * j < per ? e0 + 64 * j : e0];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) mx = fmaxf(mx, finite_abs(v[j]));
+      for (int j = 0; j < 8; ++j) mx = fmaxf(mx, fabsf(v[j]));
     }
     mx = wave_max(mx);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = co < Co ? mx : 0.0f;
@@ -117,12 +135,20 @@ __global__ __launch_bounds__(1024) void k_mixq_weights(const float* __restrict__
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int64_t c1 = CK * ck + (CK == 32 ? 16 * (j >> 2) : 0) + 4 * g + (j & 3);
-      v[j] = co < Co && c1 < C1 ? ldexpf(W[co * per + c1 * s1 + c2 * s2], kWs - ex) : 0.0f;
+      v[j] = co < Co && c1 < C1 ? ldexpf(W[co * per + c1 * s1 + c2 * s2], kW - ex) : 0.0f;
     }
-    const u4 a = split4(v[0], v[1], v[2], v[3]), b = split4(v[4], v[5], v[6], v[7]);
-    u4* const o = img + ((ct * nck + ck) * C2 + c2) * 128 + lane;
-    o[0] = u4{a[0], a[1], b[0], b[1]};
-    o[64] = u4{a[2], a[3], b[2], b[3]};
+    u4 p[3];
+    split3x8(v, p);
+    u4* const o = img + ((ct * nck + ck) * C2 + c2) * 192 + lane;
+    if constexpr (CK == 32) {
+      o[0] = p[0];
+      o[64] = p[1];
+      o[128] = p[2];
+    } else {
+      o[0] = p[0];  // (j and j + 4 are the same channel)
+      o[64] = p[1];
+      o[128] = u4{p[0][0], p[0][1], p[2][0], p[2][1]};
+    }
   }
 }
 
@@ -131,18 +157,19 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     const TX* __restrict__ x1, const TX* __restrict__ x2, const u4* __restrict__ img, const int* __restrict__ ew,
     float* __restrict__ y, int64_t B, int64_t C1, int64_t C2, int64_t Co) {
   using G = MixqGeo<L>;
-  constexpr int ka = MixqImages<L>::ka;
   const u4* const yimg = reinterpret_cast<const u4*>(MixqImages<L>::get());
   constexpr int K = G::K, S = K | 1, T = G::T, NB = G::NB, U = NB * T, KS = G::KS, NWQ = G::NWQ;
-  // a wave's own LDS: 32 staged rows, then F2's columns, then its sampled sums
-  constexpr int REG = (32 * S > 32 * 16 * U ? 32 * S : 32 * 16 * U);
-  static_assert(REG * 4 >= 8192 && T <= 8, "the sampled sums of a 16-row tile in the wave's region");
-  __shared__ __align__(16) float lds[NWQ * REG + NWQ * 16];
-  lds_poison(lds, NWQ * REG + NWQ * 16);
+  constexpr int XP = sizeof(TX) == 2 ? 1 : 3;  // parts of an input value
+  // a wave's own LDS: 32 staged rows and, in their place (after them where
+  // several batch entries are staged in turn), F2's columns; then its sampled sums
+  constexpr int F2 = NB > 1 ? 32 * S : 0, STG = 32 * S > F2 + 32 * 16 * U ? 32 * S : F2 + 32 * 16 * U;
+  constexpr int REG = ((STG > 3072 ? STG : 3072) + 3) / 4 * 4;  // three parts of the sums of a 16-row tile: 3072
+  static_assert(T <= 8, "one operand holds the wave's tiles");
+  __shared__ __align__(16) float lds[NWQ * REG];
+  lds_poison(lds, NWQ * REG);
   const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* const st = lds + wave * REG;
-  float* const mxb = lds + NWQ * REG;  // the output rows' maxima per wave
   const int64_t b0 = int64_t(blockIdx.x) * NB;
   const int64_t nc1 = (C1 + CK - 1) / CK;
 
@@ -161,20 +188,19 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
           const int64_t e = e0 + 64 * decltype(J)::value;
           v[decltype(J)::value] = mq_ld(r, e < n ? e : n - 1);
         });
-        cfor<0, 8>([&](auto J) { m = fmaxf(m, finite_abs(v[decltype(J)::value])); });
+        cfor<0, 8>([&](auto J) { m = fmaxf(m, fabsf(v[decltype(J)::value])); });
       }
       return __builtin_amdgcn_readfirstlane(exponent_of(wave_max(m)));
     };
-    e1[b] = one1 ? kNone : largest(x1 + bb * C1 * K, C1 * K);
-    e2[b] = one2 ? kNone : largest(x2 + bb * C2 * K, C2 * K);
+    e1[b] = one1 ? 0 : largest(x1 + bb * C1 * K, C1 * K);
+    e2[b] = one2 ? 0 : largest(x2 + bb * C2 * K, C2 * K);
   });
 
   // samples of the channels c0 .. c0 + 16 RT - 1 of batch entry b at this
-  // wave's points, each channel times 2^(kXs + kYs) over its own power of two:
-  // out(tile, row tile, values, exponents), rows = channels (register r of lane
-  // group g: channel c0 + 16 rt + 4 g + r), columns = points; before them
-  // all(e), the largest of the exponents, where these are all C channels
-  auto sample = [&](auto RTC, const TX* x, int64_t C, int64_t c0, int b, auto&& all, auto&& out) {
+  // wave's points, times 2^(top - e): out(tile, row tile, values), rows =
+  // channels (register r of lane group g: channel c0 + 16 rt + 4 g + r), columns
+  // = points.  own: these are all C channels, e is found here.
+  auto sample = [&](auto RTC, const TX* x, int64_t C, int64_t c0, int b, int top, int& e, bool own, auto&& out) {
     constexpr int RT = decltype(RTC)::value, NR = 16 * RT;
     int lane = threadIdx.x & 63;
     hold(lane);  // or the addresses of all stages are made ahead and spilled
@@ -182,6 +208,7 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
     const int64_t bb = b0 + b < B ? b0 + b : B - 1;
     const int rows = int(C - c0 < NR ? C - c0 : NR);
     const TX* const xr = x + (bb * C + c0) * K;
+    lds_exchange();
     {
       constexpr int NL = (NR * K + 63) / 64;
       float v[NL];
@@ -190,47 +217,21 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
         const int q = lane + 64 * decltype(J)::value;
         v[decltype(J)::value] = mq_ld(xr, q < last ? q : last);
       });
+      if (own) {
+        float m = 0.0f;
+        cfor<0, NL>([&](auto J) { m = fmaxf(m, fabsf(v[decltype(J)::value])); });
+        e = __builtin_amdgcn_readfirstlane(exponent_of(wave_max(m)));
+      }
       cfor<0, NL>([&](auto J) {
         const int q = lane + 64 * decltype(J)::value;
-        float w = q <= last ? v[decltype(J)::value] : 0.0f;
+        float w = q <= last ? ldexpf(v[decltype(J)::value], top - e) : 0.0f;
         hold(w);
         if (q < NR * K) st[S == K ? q : q / K * S + q % K] = w;
       });
     }
-    // the rows' exponents: 64 / NR lanes to a row
-    float mx = 0.0f;
-    int bad = 0;
-    cfor<0, (K + 64 / NR - 1) / (64 / NR)>([&](auto J) {
-      const int k = lane / NR + 64 / NR * decltype(J)::value;
-      const float w = st[(lane % NR) * S + (k < K ? k : 0)];
-      mx = fmaxf(mx, finite_abs(w));
-      bad |= !(fabsf(w) < __builtin_inff());
-    });
-#pragma unroll
-    for (int d = NR; d < 64; d *= 2) {
-      mx = fmaxf(mx, __shfl_xor(mx, d));
-      bad |= __shfl_xor(bad, d);
-    }
-    const int er = bad ? kBad : exponent_of(mx);
-    if (C <= NR) {
-      int em = bad ? kNone : er;
-#pragma unroll
-      for (int d = 1; d < NR; d *= 2) {
-        const int o = __shfl_xor(em, d);
-        em = o > em ? o : em;
-      }
-      all(__builtin_amdgcn_readfirstlane(em));
-    }
-    int ed[RT][4];  // of the result rows
+    lds_exchange();
+    u4 a[RT][KS][XP];
     cfor<0, RT>([&](auto RR) {
-      cfor<0, 4>([&](auto R) {
-        ed[decltype(RR)::value][decltype(R)::value] =
-            __shfl(er, 16 * decltype(RR)::value + 4 * g + decltype(R)::value);
-      });
-    });
-    u4 a[RT][KS][2];
-    cfor<0, RT>([&](auto RR) {
-      const int es = __shfl(er, 16 * decltype(RR)::value + i), ea = kXs - (es == kBad ? 0 : es);
       cfor<0, KS>([&](auto SS) {
         constexpr int rt = decltype(RR)::value, s = decltype(SS)::value;
         float v[8];
@@ -239,55 +240,48 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
           const int k = 32 * s + 8 * g + j;
           float w = st[(16 * rt + i) * S + (k < K ? k : 0)];
           hold(w);  // read by every lane, then selected: no branch
-          v[j] = k < K ? ldexpf(w, ea) : 0.0f;
+          v[j] = k < K ? w : 0.0f;
         });
-        const u4 p = split4(v[0], v[1], v[2], v[3]), q = split4(v[4], v[5], v[6], v[7]);
-        a[rt][s][0] = u4{p[0], p[1], q[0], q[1]};
-        a[rt][s][1] = u4{p[2], p[3], q[2], q[3]};
+        u4 p[3];
+        split3x8(v, p);
+        cfor<0, XP>([&](auto PP) { a[rt][s][decltype(PP)::value] = p[decltype(PP)::value]; });
       });
     });
-    // the points' values a tile ahead
-    const u4* const yt = yimg + G::YS / 8 + wave * T * KS * 128 + lane;
-    u4 yn[KS][2];
-    cfor<0, KS>([&](auto SS) {
-      yn[decltype(SS)::value][0] = yt[decltype(SS)::value * 128];
-      yn[decltype(SS)::value][1] = yt[decltype(SS)::value * 128 + 64];
-    });
+    lds_exchange();
+    // the points' values, a tile ahead where the registers allow
+    constexpr bool AHEAD = KS < 3;
+    const u4* const yt = yimg + G::YS / 8 + wave * T * KS * 192 + lane;
+    u4 yn[AHEAD ? KS : 1][3];
+    if constexpr (AHEAD)
+      cfor<0, 3 * KS>([&](auto Q) { yn[decltype(Q)::value / 3][decltype(Q)::value % 3] = yt[decltype(Q)::value * 64]; });
     cfor<0, T>([&](auto TT) {
       constexpr int t = decltype(TT)::value;
-      u4 yv[KS][2];
-      cfor<0, KS>([&](auto SS) {
-        constexpr int s = decltype(SS)::value;
-        yv[s][0] = yn[s][0];
-        yv[s][1] = yn[s][1];
-        if constexpr (t + 1 < T) {
-          yn[s][0] = yt[((t + 1) * KS + s) * 128];
-          yn[s][1] = yt[((t + 1) * KS + s) * 128 + 64];
+      u4 yv[KS][3];
+      cfor<0, 3 * KS>([&](auto Q) {
+        constexpr int s = decltype(Q)::value / 3, p = decltype(Q)::value % 3;
+        if constexpr (AHEAD) {
+          yv[s][p] = yn[s][p];
+          if constexpr (t + 1 < T) yn[s][p] = yt[((t + 1) * KS * 3 + decltype(Q)::value) * 64];
+        } else {
+          yv[s][p] = yt[(t * KS * 3 + decltype(Q)::value) * 64];
         }
       });
       __builtin_amdgcn_sched_barrier(0);
       f4 d[RT];
       cfor<0, RT>([&](auto RR) { d[decltype(RR)::value] = f4{0.0f, 0.0f, 0.0f, 0.0f}; });
-      cfor<0, KS>([&](auto SS) {
-        constexpr int s = decltype(SS)::value;
-        cfor<0, RT>([&](auto RR) {
-          constexpr int rt = decltype(RR)::value;
-          d[rt] = mfma(a[rt][s][0], yv[s][1], d[rt]);
-        });
-        cfor<0, RT>([&](auto RR) {
-          constexpr int rt = decltype(RR)::value;
-          d[rt] = mfma(a[rt][s][1], yv[s][0], d[rt]);
-        });
-      });
-      // the large terms last: one rounding of the sum per instruction
-      cfor<0, KS>([&](auto SS) {
-        constexpr int s = decltype(SS)::value;
-        cfor<0, RT>([&](auto RR) {
-          constexpr int rt = decltype(RR)::value;
-          d[rt] = mfma(a[rt][s][0], yv[s][0], d[rt]);
-        });
-      });
-      cfor<0, RT>([&](auto RR) { out(TT, RR, d[decltype(RR)::value], ed[decltype(RR)::value]); });
+      // the small terms of all steps first, then the large ones: one rounding
+      // of the sum per instruction
+      auto add = [&](auto PX, auto PY) {
+        if constexpr (decltype(PX)::value < XP)
+          cfor<0, KS>([&](auto SS) {
+            cfor<0, RT>([&](auto RR) {
+              constexpr int rt = decltype(RR)::value, s = decltype(SS)::value;
+              d[rt] = mfma_bf(a[rt][s][decltype(PX)::value < XP ? decltype(PX)::value : 0], yv[s][decltype(PY)::value], d[rt]);
+            });
+          });
+      };
+      each_pair(add);
+      cfor<0, RT>([&](auto RR) { out(TT, RR, d[decltype(RR)::value]); });
     });
   };
 
@@ -296,201 +290,124 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
   cfor<0, U>([&](auto UU) {
     cfor<0, NCOT>([&](auto CC) { acc[decltype(UU)::value][decltype(CC)::value] = f4{0.0f, 0.0f, 0.0f, 0.0f}; });
   });
-  // turns: the channels of x1 whose exponents lie in (ec - kClass, ec], from
-  // the largest down; done when no channel is left below
-  int ec[NB];
-  cfor<0, NB>([&](auto BB) { ec[decltype(BB)::value] = e1[decltype(BB)::value]; });
-  for (bool first = true, more = true; more; first = false) {
-    int below[NB];  // the largest exponent under this turn's
-    cfor<0, NB>([&](auto BB) { below[decltype(BB)::value] = kNone; });
-    for (int64_t ck = 0; ck < nc1; ++ck) {
-      u4 f1[U][2];  // F1 as operands: parts 1 and 2 of eight channels (CK = 32), or both of four
+  constexpr int FP = CK == 32 ? 3 : 2;
+  for (int64_t ck = 0; ck < nc1; ++ck) {
+    // F1 as operands: CK = 32: the three parts of eight channels; CK = 16: parts
+    // (1, 2) and (3, 1) of four
+    u4 f1[U][FP];
+    cfor<0, NB>([&](auto BB) {
+      constexpr int b = decltype(BB)::value;
+      f4 lo;
+      sample(std::integral_constant<int, CK / 16>{}, x1, C1, ck * CK, b, kX1, e1[b], one1, [&](auto TT, auto RR, f4 d) {
+        constexpr int u = b * T + decltype(TT)::value;
+        if constexpr (CK == 16) {
+          uint32_t p[2], q[2], r[2];
+          split3(d[0], d[1], p[0], q[0], r[0]);
+          split3(d[2], d[3], p[1], q[1], r[1]);
+          f1[u][0] = u4{p[0], p[1], q[0], q[1]};
+          f1[u][1] = u4{r[0], r[1], p[0], p[1]};
+        } else if constexpr (decltype(RR)::value == 0) {
+          lo = d;
+        } else {
+          split3x8({lo[0], lo[1], lo[2], lo[3], d[0], d[1], d[2], d[3]}, f1[u]);
+        }
+      });
+    });
+    for (int64_t c20 = 0; c20 < C2; c20 += 32) {
+      const int n2 = int(C2 - c20 < 32 ? C2 - c20 : 32);
+      // F2 of the next 32 channels to LDS [channel][tile, point]
       cfor<0, NB>([&](auto BB) {
         constexpr int b = decltype(BB)::value;
-        f4 lo[T];
-        int under = kNone;
-        auto all = [&](int e) {
-          e1[b] = e;
-          if (first) ec[b] = e;
-        };
-        sample(std::integral_constant<int, CK / 16>{}, x1, C1, ck * CK, b, all,
-               [&](auto TT, auto RR, f4 d, const int (&e)[4]) {
-          constexpr int t = decltype(TT)::value, u = b * T + t;
+        sample(std::integral_constant<int, 2>{}, x2, C2, c20, b, kX2, e2[b], one2, [&](auto TT, auto RR, f4 d) {
           cfor<0, 4>([&](auto R) {
-            constexpr int r = decltype(R)::value;
-            const int rel = e[r] - ec[b];
-            // (a NaN or Inf reaches every sample of its channel, and stands)
-            if (e[r] != kBad) d[r] = rel <= 0 && rel > -kClass ? ldexpf(d[r], rel) : 0.0f;
-            if constexpr (t == 0) {
-              if (rel <= -kClass) under = e[r] > under ? e[r] : under;
-            }
+            constexpr int rt = decltype(RR)::value, r = decltype(R)::value, u = b * T + decltype(TT)::value;
+            st[F2 + (16 * rt + 4 * g + r) * (16 * U) + 16 * u + i] = d[r];
           });
-          if constexpr (CK == 16) {
-            f1[u][0] = split4(d[0], d[1], d[2], d[3]);
-          } else if constexpr (decltype(RR)::value == 0) {
-            lo[t] = d;
-          } else {
-            const u4 p = split4(lo[t][0], lo[t][1], lo[t][2], lo[t][3]), q = split4(d[0], d[1], d[2], d[3]);
-            f1[u][0] = u4{p[0], p[1], q[0], q[1]};
-            f1[u][1] = u4{p[2], p[3], q[2], q[3]};
-          }
         });
-  #pragma unroll
-        for (int d = 16; d < 64; d *= 2) {
-          const int o = __shfl_xor(under, d);
-          under = o > under ? o : under;
-        }
-        under = __builtin_amdgcn_readfirstlane(under);
-        below[b] = under > below[b] ? under : below[b];
       });
-      for (int64_t c20 = 0; c20 < C2; c20 += 32) {
-        const int n2 = int(C2 - c20 < 32 ? C2 - c20 : 32);
-        // F2 of the next 32 channels over its input's power of two, and the
-        // contraction's scales taken back, to LDS [channel][tile, point]
-        f4 f2[U][2];
-        cfor<0, NB>([&](auto BB) {
-          constexpr int b = decltype(BB)::value;
-          int back = 0;
-          auto all = [&](int e) { e2[b] = e; };
-          sample(std::integral_constant<int, 2>{}, x2, C2, c20, b, all, [&](auto TT, auto RR, f4 d, const int (&e)[4]) {
-            if constexpr (decltype(TT)::value == 0 && decltype(RR)::value == 0)
-              back = ec[b] - e1[b] - e2[b] - 2 * (kXs + kYs) - kWs;
-            cfor<0, 4>([&](auto R) {
-              constexpr int r = decltype(R)::value;
-              d[r] = ldexpf(d[r], e[r] + back);
-            });
-            f2[b * T + decltype(TT)::value][decltype(RR)::value] = d;
+      lds_exchange();
+      const u4* wp[NCOT];
+      cfor<0, NCOT>([&](auto CC) {
+        constexpr int cc = decltype(CC)::value;
+        const int64_t ct = ct0 + cc < (Co + 15) / 16 ? ct0 + cc : ct0;
+        wp[cc] = img + ((ct * nc1 + ck) * C2 + c20) * 192 + lane;
+      });
+      // the weights PD channels ahead, as the registers allow
+      constexpr int PD = U * NCOT <= 4 ? 4 : U * NCOT <= 8 ? 2 : 1;
+      u4 wr[PD][NCOT][3];
+      cfor<0, PD>([&](auto PP) {
+        constexpr int j = decltype(PP)::value;
+        const int cn = j < n2 ? j : n2 - 1;
+        cfor<0, 3 * NCOT>([&](auto Q) {
+          constexpr int cc = decltype(Q)::value / 3, p = decltype(Q)::value % 3;
+          wr[j][cc][p] = wp[cc][cn * 192 + 64 * p];
+        });
+      });
+      for (int cb = 0; cb < n2; cb += PD) {
+        cfor<0, PD>([&](auto JJ) {
+          constexpr int ring = decltype(JJ)::value;
+          const int c = cb + ring;
+          if (PD > 1 && c >= n2) return;
+          u4 w[NCOT][3];
+          const int cn = c + PD < n2 ? c + PD : n2 - 1;
+          cfor<0, 3 * NCOT>([&](auto Q) {
+            constexpr int cc = decltype(Q)::value / 3, p = decltype(Q)::value % 3;
+            w[cc][p] = wr[ring][cc][p];
+            wr[ring][cc][p] = wp[cc][cn * 192 + 64 * p];
           });
-        });
-        cfor<0, 2>([&](auto RR) {
-          cfor<0, 4>([&](auto R) {
-            constexpr int rt = decltype(RR)::value, r = decltype(R)::value;
-            cfor<0, U>([&](auto UU) {
-              constexpr int u = decltype(UU)::value;
-              st[(16 * rt + 4 * g + r) * (16 * U) + 16 * u + i] = f2[u][rt][r];
+          float f[U];
+          cfor<0, U>([&](auto UU) { f[decltype(UU)::value] = st[F2 + c * (16 * U) + 16 * decltype(UU)::value + i]; });
+          // GU tiles at a time, so that no instruction waits for the one before
+          constexpr int GU = NCOT == 1 ? 4 : 2;
+          cfor<0, (U + GU - 1) / GU>([&](auto PP) {
+            constexpr int u0 = GU * decltype(PP)::value, nu = U - u0 < GU ? U - u0 : GU;
+            f4 d[nu][NCOT];
+            cfor<0, nu * NCOT>([&](auto Q) {
+              d[decltype(Q)::value / NCOT][decltype(Q)::value % NCOT] = f4{0.0f, 0.0f, 0.0f, 0.0f};
             });
-          });
-        });
-        const u4* wp[NCOT];
-        cfor<0, NCOT>([&](auto CC) {
-          constexpr int cc = decltype(CC)::value;
-          const int64_t ct = ct0 + cc < (Co + 15) / 16 ? ct0 + cc : ct0;
-          wp[cc] = img + ((ct * nc1 + ck) * C2 + c20) * 128 + lane;
-        });
-        // the weights PD channels ahead, as the registers allow
-        constexpr int PD = U * NCOT <= 4 ? 4 : U * NCOT <= 8 ? 2 : 1;
-        u4 wr[PD][NCOT][2];
-        cfor<0, PD>([&](auto PP) {
-          constexpr int j = decltype(PP)::value;
-          const int cn = j < n2 ? j : n2 - 1;
-          cfor<0, NCOT>([&](auto CC) {
-            constexpr int cc = decltype(CC)::value;
-            wr[j][cc][0] = wp[cc][cn * 128];
-            wr[j][cc][1] = wp[cc][cn * 128 + 64];
-          });
-        });
-        for (int cb = 0; cb < n2; cb += PD) {
-          cfor<0, PD>([&](auto JJ) {
-            constexpr int ring = decltype(JJ)::value;
-            const int c = cb + ring;
-            if (PD > 1 && c >= n2) return;
-            u4 w[NCOT][2];
-            const int cn = c + PD < n2 ? c + PD : n2 - 1;
-            cfor<0, NCOT>([&](auto CC) {
-              constexpr int cc = decltype(CC)::value;
-              w[cc][0] = wr[ring][cc][0];
-              w[cc][1] = wr[ring][cc][1];
-              wr[ring][cc][0] = wp[cc][cn * 128];
-              wr[ring][cc][1] = wp[cc][cn * 128 + 64];
-            });
-            float f[U];
-            cfor<0, U>([&](auto UU) { f[decltype(UU)::value] = st[c * (16 * U) + 16 * decltype(UU)::value + i]; });
-            // GU tiles at a time, so that no instruction waits for the one before
-            constexpr int GU = NCOT == 1 ? 4 : 2;
-            cfor<0, (U + GU - 1) / GU>([&](auto PP) {
-              constexpr int u0 = GU * decltype(PP)::value, nu = U - u0 < GU ? U - u0 : GU;
-              f4 d[nu][NCOT];
-              cfor<0, nu>([&](auto UU) {
-                cfor<0, NCOT>([&](auto CC) {
-                  d[decltype(UU)::value][decltype(CC)::value] =
-                      mfma(w[decltype(CC)::value][1], f1[u0 + decltype(UU)::value][0], f4{0.0f, 0.0f, 0.0f, 0.0f});
-                });
+            auto add = [&](auto PW, auto PF) {
+              cfor<0, nu * NCOT>([&](auto Q) {
+                constexpr int u = decltype(Q)::value / NCOT, cc = decltype(Q)::value % NCOT;
+                d[u][cc] = mfma_bf(w[cc][decltype(PW)::value], f1[u0 + u][decltype(PF)::value], d[u][cc]);
               });
-              if constexpr (CK == 32)
-                cfor<0, nu>([&](auto UU) {
-                  cfor<0, NCOT>([&](auto CC) {
-                    f4& r = d[decltype(UU)::value][decltype(CC)::value];
-                    r = mfma(w[decltype(CC)::value][0], f1[u0 + decltype(UU)::value][1], r);
-                  });
-                });
-              cfor<0, nu>([&](auto UU) {
-                cfor<0, NCOT>([&](auto CC) {
-                  f4& r = d[decltype(UU)::value][decltype(CC)::value];
-                  r = mfma(w[decltype(CC)::value][0], f1[u0 + decltype(UU)::value][0], r);
-                });
-              });
-              cfor<0, nu>([&](auto UU) {
-                cfor<0, NCOT>([&](auto CC) {
-                  constexpr int u = u0 + decltype(UU)::value;
-                  acc[u][decltype(CC)::value] += f[u] * d[decltype(UU)::value][decltype(CC)::value];
-                });
-              });
-              __builtin_amdgcn_sched_barrier(0);
+            };
+            if constexpr (CK == 32) {
+              each_pair(add);
+            } else {
+              add(std::integral_constant<int, 2>{}, std::integral_constant<int, 1>{});  // 1 x 3, 3 x 1
+              add(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{});  // 2 x 1, 2 x 2
+              add(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});  // 1 x 1, 1 x 2
+            }
+            cfor<0, nu * NCOT>([&](auto Q) {
+              constexpr int u = decltype(Q)::value / NCOT, cc = decltype(Q)::value % NCOT;
+              acc[u0 + u][cc] += f[u0 + u] * d[u][cc];
             });
             __builtin_amdgcn_sched_barrier(0);
           });
-          asm volatile("" ::: "memory");  // or the loads move down to their use
-        }
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        asm volatile("" ::: "memory");  // or the loads move down to their use
       }
     }
-    more = false;
-    cfor<0, NB>([&](auto BB) {
-      constexpr int b = decltype(BB)::value;
-      more = more || below[b] > kNone;
-      ec[b] = below[b] > kNone ? below[b] : kDone;
-    });
   }
   // ---- analysis, one batch entry and 16 output channels at a time
   cfor<0, NB>([&](auto BB) {
     cfor<0, NCOT>([&](auto CC) {
       constexpr int b = decltype(BB)::value, cc = decltype(CC)::value;
       const int64_t co0 = 16 * (ct0 + cc);
-      // an exponent for each output row: one output channel's sums may lie any
-      // way below another's
-      int eg[4];
-      cfor<0, 4>([&](auto R) {
-        constexpr int r = decltype(R)::value;
-        float mx = 0.0f;
-        cfor<0, T>([&](auto TT) { mx = fmaxf(mx, finite_abs(acc[b * T + decltype(TT)::value][cc][r])); });
-#pragma unroll
-        for (int d = 1; d < 16; d *= 2) mx = fmaxf(mx, __shfl_xor(mx, d));
-        if constexpr (NWQ > 1) {
-          if (i == 0) mxb[wave * 16 + 4 * g + r] = mx;
-        } else {
-          eg[r] = exponent_of(mx);
-        }
-      });
-      if constexpr (NWQ > 1) {
-        __syncthreads();
-        cfor<0, 4>([&](auto R) {
-          constexpr int r = decltype(R)::value;
-          float mx = 0.0f;
-          cfor<0, NWQ>([&](auto W) { mx = fmaxf(mx, mxb[decltype(W)::value * 16 + 4 * g + r]); });
-          eg[r] = exponent_of(mx);
-        });
-      }
-      // parts 1, then 2: [row][point of the tile][tile]
+      // the three parts: [part][row][point of the tile][tile]
+      lds_exchange();
       u4* const gs = reinterpret_cast<u4*>(st);
       cfor<0, 4>([&](auto R) {
         constexpr int r = decltype(R)::value;
         float v[8];
         cfor<0, 8>([&](auto TT) {
           constexpr int t = decltype(TT)::value;
-          v[t] = t < T ? ldexpf(acc[b * T + (t < T ? t : 0)][cc][r], kGs - eg[r]) : 0.0f;
+          v[t] = t < T ? acc[b * T + (t < T ? t : 0)][cc][r] : 0.0f;
         });
-        const u4 p = split4(v[0], v[1], v[2], v[3]), q = split4(v[4], v[5], v[6], v[7]);
-        gs[(4 * g + r) * 16 + i] = u4{p[0], p[1], q[0], q[1]};
-        gs[256 + (4 * g + r) * 16 + i] = u4{p[2], p[3], q[2], q[3]};
+        u4 p[3];
+        split3x8(v, p);
+        cfor<0, 3>([&](auto PP) { gs[256 * decltype(PP)::value + (4 * g + r) * 16 + i] = p[decltype(PP)::value]; });
       });
       __syncthreads();
       for (int kt = wave; kt < G::KT; kt += NWQ) {
@@ -498,38 +415,40 @@ __global__ __launch_bounds__(64 * MixqGeo<L>::NWQ) __attribute__((amdgpu_waves_p
         f4 d = {0.0f, 0.0f, 0.0f, 0.0f}, hi[NWQ][2];
         cfor<0, NWQ>([&](auto WW) {
           constexpr int w = decltype(WW)::value;
-          u4 ya[4][2];  // a wave's points at a time, all loads first
-          cfor<0, 4>([&](auto SS) {
-            constexpr int s = decltype(SS)::value;
-            ya[s][0] = yimg[G::YA / 8 + (kt * NWQ * 4 + 4 * w + s) * 128 + lane];
-            ya[s][1] = yimg[G::YA / 8 + (kt * NWQ * 4 + 4 * w + s) * 128 + 64 + lane];
+          u4 ya[4][3];  // a wave's points at a time, all loads first
+          cfor<0, 12>([&](auto Q) {
+            ya[decltype(Q)::value / 3][decltype(Q)::value % 3] =
+                yimg[G::YA / 8 + ((kt * NWQ + w) * 12 + decltype(Q)::value) * 64 + lane];
           });
           cfor<0, 4>([&](auto SS) {
             constexpr int s = decltype(SS)::value;
             const u4* const ga = reinterpret_cast<const u4*>(lds + w * REG) + i * 16 + 4 * s + g;
-            const u4 a1 = ga[0], a2 = ga[256];
-            d = mfma(a1, ya[s][1], d);
-            d = mfma(a2, ya[s][0], d);
-            hi[w][s / 2] = mfma(a1, ya[s][0], s % 2 ? hi[w][s / 2] : f4{0.0f, 0.0f, 0.0f, 0.0f});
+            const u4 a[3] = {ga[0], ga[256], ga[512]};
+            each_pair([&](auto PA, auto PY) {
+              constexpr int pa = decltype(PA)::value, py = decltype(PY)::value;
+              if constexpr (pa + py > 0) d = mfma_bf(a[pa], ya[s][py], d);
+            });
+            hi[w][s / 2] = mfma_bf(a[0], ya[s][0], s % 2 ? hi[w][s / 2] : f4{0.0f, 0.0f, 0.0f, 0.0f});
           });
           hi[w][0] += hi[w][1];
           if constexpr (w > 0) hi[0][0] += hi[w][0];
+          __builtin_amdgcn_sched_barrier(0);  // one wave's points in registers at a time
         });
         d += hi[0][0];
-        const int k = 16 * kt + i, ex = e1[b] + e2[b] - kGs - ka;
+        const int k = 16 * kt + i, ex = e1[b] + e2[b] - kX1 - kW - kX2;
         cfor<0, 4>([&](auto R) {
           constexpr int r = decltype(R)::value;
           const int64_t co = co0 + 4 * g + r;
-          if (b0 + b < B && co < Co && k < K) y[((b0 + b) * Co + co) * K + k] = ldexpf(d[r], ex + eg[r] + ew[co]);
+          if (b0 + b < B && co < Co && k < K) y[((b0 + b) * Co + co) * K + k] = ldexpf(d[r], ex + ew[co]);
         });
       }
-      __syncthreads();  // the regions are read: the next rows, or stage, may land there
+      __syncthreads();  // the regions are read: the next rows may land there
     });
   });
 }
 
 int64_t image_bytes(int64_t Co, int64_t C1, int64_t C2) {
-  return (Co + 15) / 16 * (C1 <= 16 ? 1 : (C1 + 31) / 32) * C2 * 2048;
+  return (Co + 15) / 16 * (C1 <= 16 ? 1 : (C1 + 31) / 32) * C2 * 3072;
 }
 
 template <int L, typename TX, int CK, int NCOT>
@@ -562,7 +481,7 @@ hipError_t launch_degree(const MixqArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int64_t mixq_steps(int64_t C) { return C <= 16 ? 2 : 3 * ((C + 31) / 32); }
+int64_t mixq_steps(int64_t C) { return C <= 16 ? 3 : 6 * ((C + 31) / 32); }
 
 int64_t mixq_work_bytes(int64_t Co, int64_t C1, int64_t C2) {
   return image_bytes(Co, C1, C2) + (Co + 15) / 16 * 64;

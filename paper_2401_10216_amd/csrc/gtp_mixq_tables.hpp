@@ -5,20 +5,18 @@
 // 1 uniform phi, exact for the triple products' degree 3 L; the Q points are
 // numbered in TILES tiles of 16 (the last one's rest is padding, zero in every
 // image), T tiles to a wave and NWQ waves to a batch entry.  Images of
-// v_mfma_f32_16x16x32_f16 operands in two fp16 parts (gtp_mfma_tables.hpp),
-// eight halves per lane 16 g + i:
+// v_mfma_f32_16x16x32_bf16 operands in three bf16 parts (gtp_split.hpp), eight
+// values per lane 16 g + i:
 //   YS[tile][step][part]     column i = point 16 tile + i, contraction indices
-//        = coefficients 32 step + 8 g + j: 2^kYs Y_k(point)
+//        = coefficients 32 step + 8 g + j: Y_k(point)
 //   YA[ktile][wave][s][part] column i = coefficient 16 ktile + i, contraction
-//        indices = points 16 (T wave + j) + 4 s + g, j < T: 2^ka w Y_k(point)
+//        indices = points 16 (T wave + j) + 4 s + g, j < T: w Y_k(point)
 #pragma once
 
 #include <cstdint>
 #include <vector>
 
 namespace gtp {
-
-constexpr int kYs = 4;
 
 template <int L>
 struct MixqGeo {
@@ -30,11 +28,15 @@ struct MixqGeo {
   static constexpr int NWQ = L <= 4 ? 1 : L <= 6 ? 2 : 4;
   static constexpr int T = (TILES + NWQ - 1) / NWQ, NB = L == 1 ? 4 : L == 2 ? 2 : 1;
   static constexpr int KS = (K + 31) / 32, KT = (K + 15) / 16;
-  static constexpr int FR = 64 * 8;  // halves of an image
-  static constexpr int YS = 0, YA = YS + NWQ * T * KS * 2 * FR, HALVES = YA + KT * NWQ * 4 * 2 * FR;
+  static constexpr int FR = 64 * 8;  // values of an image
+  static constexpr int YS = 0, YA = YS + NWQ * T * KS * 3 * FR, HALVES = YA + KT * NWQ * 4 * 3 * FR;
 };
 
-// The images of degree L (1..8); *ka receives the exponent of YA's scale.
-std::vector<uint16_t> build_mixq_images(int L, int* ka);
+// bf16 bits of a double (round to nearest even; normal range).
+uint16_t bf16_bits(double v);
+double bf16_value(uint16_t b);
+
+// The images of degree L (1..8).
+std::vector<uint16_t> build_mixq_images(int L);
 
 }  // namespace gtp
