@@ -481,8 +481,6 @@ hipError_t launch_degree(const MixqArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int64_t mixq_steps(int64_t C) { return C <= 16 ? 3 : 6 * ((C + 31) / 32); }
-
 int64_t mixq_work_bytes(int64_t Co, int64_t C1, int64_t C2) {
   return image_bytes(Co, C1, C2) + (Co + 15) / 16 * 64;
 }

@@ -17,9 +17,6 @@ struct MixqArgs {
   int64_t B, C1, C2, Co;
 };
 
-// Contractions per 16 points and 16 outputs with C channels as the
-// contraction index (the caller gives C1 the role that costs less).
-int64_t mixq_steps(int64_t C);
 // Size of MixqArgs::work.
 int64_t mixq_work_bytes(int64_t Co, int64_t C1, int64_t C2);
 hipError_t launch_mixq(int L, const MixqArgs& a, hipStream_t s, bool* supported);

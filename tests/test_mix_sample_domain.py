@@ -1,5 +1,5 @@
 """Channel mixing in the sample domain (equal degrees 1..8, C1 C2 >= 128, Co <=
-128): every degree, channel counts about the 16 and 32 of the operand tiles, in
+128; the plans' hook takes it at the small sizes of these tests too): every degree, channel counts about the 16 and 32 of the operand tiles, in
 both roles of the two inputs, output channels about the 16 and 32 of a
 workgroup, batches that leave the last workgroup of the low degrees short.
 
@@ -17,6 +17,11 @@ from oracle import gtp_oracle as O  # noqa: E402
 from paper_2401_10216_amd import gtp  # noqa: E402
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _sampled(monkeypatch):
+    monkeypatch.setenv("GTP_TEST_MIX", "sampled")
 
 
 def _products(L, x1, x2):
@@ -167,3 +172,14 @@ def test_channels_without_a_finite_value(L, C1, C2, which):
             assert not torch.isfinite(got[b]).any(), b
         else:
             assert torch.equal(got[b], want[b]), b
+
+
+@pytest.mark.parametrize("L,B,C1,C2,Co", [(6, 512, 32, 32, 32), (1, 8192, 24, 24, 8), (8, 16, 32, 32, 32)])
+def test_the_way_that_pays_is_taken(monkeypatch, L, B, C1, C2, Co):
+    """At sizes where the sample domain pays, a plan without the hook gives its results, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(L)
+    x1, x2 = (torch.randn((B, c, (L + 1) ** 2), generator=g, device="cuda") for c in (C1, C2))
+    W = torch.randn((Co, C1, C2), generator=g, device="cuda")
+    hooked = gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W)
+    monkeypatch.delenv("GTP_TEST_MIX")
+    assert torch.equal(gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W), hooked)
