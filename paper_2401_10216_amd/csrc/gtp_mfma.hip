@@ -5,8 +5,10 @@
 // mirror pairs, 4-fold phi symmetry) with every transform a matrix
 // contraction.  The theta synthesis runs on v_mfma_f32_16x16x4_f32; the phi
 // transforms and the theta analysis on v_mfma_f32_16x16x32_f16 with split
-// operands: a value enters as h1 + h2, two halves that together carry fp32's
-// accuracy (h1 = fp16(v), h2 = fp16(v - h1): 2^-23 of v at worst), against
+// operands: a value enters as h1 + h2 (h1 = fp16(v), h2 = fp16(v - h1)), which
+// leave at most max(2^-23 |v|, 2^-25) of it: 2^-23 of the value itself from 2^-2
+// up, and below it 2^-31 of its input's norm (theta values: 2^-25 against norms
+// 2^SE1, 2^SE2), far under the rounding of the sums it enters; against
 // tables split the same way, the products accumulating in fp32; everything
 // between the contractions stays fp32.  Three or four 16x16x32 fp16
 // contractions of 16 cycles replace eight 16x16x4 fp32 ones of 32.  The theta
@@ -37,7 +39,8 @@
 // replaced (theta stages on the VALU, table reads per product): 262144
 // products of degree 32 3.59 -> 2.58 ms, 2.1M bf16 products of degree 16 5.20 ->
 // 4.57 ms, 191904 of degree 12 0.478 -> 0.400 ms; error against fp64 (2-norm)
-// 1.7e-7 -> 1.4e-7 at 32, 1.4e-7 and 1.2e-7 unchanged at 16 and 12.  (The
+// 1.7e-7 -> 1.4e-7 at 32, 1.35e-7 -> 1.29e-7 at 16, 1.18e-7 -> 1.11e-7 at 12 (1.38e-7
+// and 1.19e-7 with phi tables at scale 1).  (The
 // theta synthesis by split fp16 too measured slower at L = 16, its operands'
 // split and scaling costing more than the contractions saved, and less exact.)
 #include <type_traits>

@@ -55,7 +55,8 @@ MfmaImages images(const Tables& t) {
     return part == 0 ? h1 : half_bits(x - half_value(h1));
   };
   auto S = [&](int l, int m, int j) { return l <= L ? t.S[size_t(tri(l, m)) * t.NJ + j] : 0.0; };
-  auto W = [&](int l, int m, int j) { return l <= L ? t.W[size_t(tri(l, m)) * t.NJ + j] : 0.0; };
+  constexpr double kW = 1.0 / (G::PHI * G::PHI * G::PHI);
+  auto W = [&](int l, int m, int j) { return l <= L ? kW * t.W[size_t(tri(l, m)) * t.NJ + j] : 0.0; };
   double wmax = 0.0;
   for (int l = 0; l <= L; ++l)
     for (int m = 0; m <= l; ++m)
@@ -66,7 +67,7 @@ MfmaImages images(const Tables& t) {
   const double wscale = std::ldexp(1.0, r.kw);
   auto trig = [&](bool sine, int m, int k) {
     const double a = kTwoPi * double((int64_t(m) * k) % G::NP) / G::NP;
-    return sine ? std::sin(a) : std::cos(a);
+    return G::PHI * (sine ? std::sin(a) : std::cos(a));
   };
   for (int lane = 0; lane < 64; ++lane) {
     const int g = lane / 16, i = lane % 16;
@@ -84,7 +85,7 @@ MfmaImages images(const Tables& t) {
         const int l = 2 * (4 * s + g) + task % 2;
         const bool pole = task >= 2 * G::NPT;
         r.f[G::S0 + ((size_t(task) * G::S0V + s / 4) * 64 + lane) * 4 + s % 4] =
-            pole ? (i == 0 ? S(l, 0, 0) : 0.0) : S(l, 0, 16 * (task / 2) + i + 1);
+            pole ? (i == 0 ? S(l, 0, 0) : 0.0) : G::PHI * S(l, 0, 16 * (task / 2) + i + 1);
       }
     for (int j = 0; j < 8; ++j) {
       auto put = [&](int base, int frag, uint16_t h) { r.h[size_t(base) + (size_t(frag) * 64 + lane) * 8 + j] = h; };

@@ -35,6 +35,12 @@
 //        8 g + j + 1, groups 2, 3 part 2 of pairs 8 (g - 2) + j + 1
 //   W0[x][part][lane][8]     the same for m = 0: x < NE0 even degrees l = 2 (16
 //        x + i), the others odd ones
+// The phi tables TP and TA are stored times PHI, the m = 0 values that meet TP's
+// sums (S0, not the poles) too, and W over PHI^3 (two syntheses, one analysis):
+// two fp16 parts leave up to 2^-23 of an entry, twice fp32's rounding, but the
+// 52 samples of L = 16 have only 13 different magnitudes, and there is a scale at
+// which all of them have short expansions (5.4e-9 rms and 1.0e-8 at most are
+// left, 2.9e-8 and 6.0e-8 at scale 1, 1.4e-8 rms in fp32).
 // W is stored times 2^kw (largest entry in [2^10, 2^11)), so that the second
 // parts of its typical entries stay normal halves.
 //
@@ -82,6 +88,7 @@ struct MfmaGeo {
   static constexpr int TAI = L == 16 ? 1 : 2;     // stored images per phi-analysis operand
   static constexpr int WPARTS = L == 16 ? 1 : 2;  // and per theta-analysis operand
   static constexpr int FR = 64 * 8;               // halves of one image
+  static constexpr double PHI = L == 16 ? 14910466.0 / 16777216.0 : 1.0;
   static constexpr int TP = 0, TA = TP + 4 * NMB * FR, WC = TA + 4 * TAI * FR, W0 = WC + NQ * 8 * WPARTS * FR,
                        HALVES = W0 + NPART * WPARTS * FR;
   // index images: halves of the gather, words of the scatter, per thread

@@ -47,7 +47,7 @@ void degree() {
         for (int i = 0; i < 16; ++i)
           for (int pair = 1; pair <= L; ++pair) {
             const int l = m + par + 2 * i, c = q * 8 + 2 * mi + par, g = (pair - 1) / 8, j = (pair - 1) % 8;
-            const double w = l <= L ? wscale * t.W[size_t(gtp::tri(l, m)) * t.NJ + pair] : 0.0;
+            const double w = l <= L ? wscale * t.W[size_t(gtp::tri(l, m)) * t.NJ + pair] / (G::PHI * G::PHI * G::PHI) : 0.0;
             const double v = L == 16 ? half(G::WC, c, 16 * g + i, j) + half(G::WC, c, 16 * (g + 2) + i, j)
                                      : half(G::WC, c * 2, 16 * g + i, j) + half(G::WC, c * 2 + 1, 16 * g + i, j);
             check(std::fabs(v - w) <= std::fmax(std::ldexp(std::fabs(w), -22), std::ldexp(1.0, -25)), "analysis entry");
@@ -56,6 +56,25 @@ void degree() {
   for (int m = 1; m <= L; ++m) check(seen[m] == 1, "order");
   for (int l = 1; l <= L; ++l)
     for (int m = 1; m <= l; ++m) check(coeff[l][m] == 1, "coefficient");
+  // the phi tables' parts: the even and odd cosines and sines of every order, and
+  // the rms of what the parts leave of them (at L = 16 below fp32's rounding, 1.4e-8)
+  double left = 0.0;
+  int entries = 0;
+  for (int type = 0; type < 4; ++type)
+    for (int mb = 0; mb < G::NMB; ++mb)
+      for (int lane = 0; lane < (L == 16 ? 32 : 64); ++lane)
+        for (int j = 0; j < 4; ++j) {
+          const int k = 16 * mb + lane % 16, q = (type & 1 ? 0 : G::NSL) + lane / 16, m = G::order(q, j);
+          if (k > G::Q) continue;
+          const double a = 6.283185307179586476925286766559 * ((m * k) % G::NP) / G::NP;
+          const double v = type >= 2 ? std::sin(a) : std::cos(a);
+          const double h = half(G::TP, type * G::NMB + mb, lane, j) +
+                           (L == 16 ? half(G::TP, type * G::NMB + mb, lane + 32, j) : half(G::TP, type * G::NMB + mb, lane, j + 4));
+          check(std::fabs(h / G::PHI - v) <= std::ldexp(1.0, -24), "phi table entry");
+          left += (h / G::PHI - v) * (h / G::PHI - v);
+          ++entries;
+        }
+  check(std::sqrt(left / entries) <= (L == 16 ? 1.0e-8 : 3.0e-8), "phi tables' rms");
   // index images: within the stage and the output image, every output once
   const int cases[][3] = {{L, L, L}, {L - 3, 2, 2 * L}, {1, L, 5}, {0, L, L}};
   for (const auto& c : cases) {

@@ -90,3 +90,20 @@ def test_scales_and_special_values(L):
     ok = [0, 1, 2, 3, 4, 5, 6, 7, 11]  # the same group's other rows are untouched
     ref = O.gtp_grid(a[ok].double().numpy(), b[ok].double().numpy(), L, L, L)
     assert O.max_rel_err(y[ok].numpy().astype(np.float64), ref) <= 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("degrees,bound", [((9, 9, 9), 1.05e-7), ((12, 12, 12), 1.18e-7), ((16, 16, 16), 1.35e-7),
+                                           ((12, 12, 5), 1.065e-7), ((20, 20, 20), 1.31e-7), ((32, 32, 32), 1.67e-7)])
+def test_error_no_larger_than_in_fp32(degrees, bound):
+    """The 2-norm error over iid N(0, 1) products against 64 bits.  The bounds
+    are what the fp32 pipeline (fp32 tables, operands and sums throughout)
+    measures for the same; over these products they move by less than 0.5 %."""
+    L1, L2, Lout = degrees
+    g = torch.Generator().manual_seed(3)
+    a, b = (torch.randn((2000 if Lout <= 16 else 400, (L + 1) ** 2), generator=g) for L in (L1, L2))
+    y = gtp.gtp_full(gtp.Plan(L1, L2, Lout), a.cuda()[:, None], b.cuda()[:, None]).cpu().numpy()[:, 0].astype(np.float64)
+    ref = O.gtp_grid(a.double().numpy(), b.double().numpy(), L1, L2, Lout)
+    err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
+    print(degrees, f"{err:.3e}", flush=True)
+    assert err <= bound, err
