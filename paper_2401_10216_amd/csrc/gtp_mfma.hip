@@ -239,6 +239,7 @@ __global__ __launch_bounds__(KGeo<L>::NTH) __attribute__((amdgpu_waves_per_eu(L 
     float xv[NX];
     {
       float ss = 0.0f;
+      uint32_t bits = 0;
       const int ti = (i >> 1) & 1;
       const float* wrow = nullptr;
       if constexpr (WGT) {
@@ -275,6 +276,7 @@ __global__ __launch_bounds__(KGeo<L>::NTH) __attribute__((amdgpu_waves_per_eu(L 
               return (L / 4) * mi + 2 * jq + (even ? 2 : 1) + pa + 2 * (4 * st + g);
             });
             ss = fmaf(v, v, ss);
+            bits |= __float_as_uint(v);
           });
         });
       });
@@ -283,8 +285,12 @@ __global__ __launch_bounds__(KGeo<L>::NTH) __attribute__((amdgpu_waves_per_eu(L 
         constexpr int st = decltype(S)::value;
         const float v = get(std::integral_constant<int, G::NSTEP + st>{}, [&] { return 2 * (4 * st + g) + wave % 2; });
         s2 = fmaf(v, v, s2);
+        bits |= __float_as_uint(v);
       });
       ss += wave < 2 ? s2 : 0.0f;  // (the other waves repeat m = 0 for other tiles and the poles)
+      // a sum of zero stands for coefficients of zero below; where only their
+      // squares vanished, for a value that is not fine
+      if (ss == 0.0f && (bits << 1) != 0) ss = 1e-38f;
       ss = add_rows(ss);
       if (g == 0) red[wave * 16 + i] = ss;
     }
@@ -319,13 +325,12 @@ __global__ __launch_bounds__(KGeo<L>::NTH) __attribute__((amdgpu_waves_per_eu(L 
       f4 ss = {0.0f, 0.0f, 0.0f, 0.0f};
       cfor<0, KG::NW>([&](auto R) { ss += *reinterpret_cast<const f4*>(red + decltype(R)::value * 16 + 4 * g); });
       const float s[2] = {ss[0] + ss[1], ss[2] + ss[3]};
-      auto fine = [](float v) { return v > 1e-30f && v < 1e37f; };
+      auto fine = [](float v) { return (v > 1e-30f && v < 1e37f) || v == 0.0f; };
       // norm in [2^(e - 1), 2^e)
       int e[2] = {(__builtin_amdgcn_frexp_expf(s[0]) + 1) >> 1, (__builtin_amdgcn_frexp_expf(s[1]) + 1) >> 1};
       if (__any(!(fine(s[0]) && fine(s[1])))) {
         // (every wave sees the same sums and takes the same way)  Where a sum
-        // of squares leaves fp32's range, and for rows of zeros: from the
-        // largest coefficient
+        // of squares leaves fp32's range: from the largest coefficient
         float mx = 0.0f;
         cfor<0, NX>([&](auto F) { mx = fmaxf(mx, fabsf(xv[decltype(F)::value])); });
         mx = max_rows(mx);

@@ -107,3 +107,29 @@ def test_error_no_larger_than_in_fp32(degrees, bound):
     err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
     print(degrees, f"{err:.3e}", flush=True)
     assert err <= bound, err
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("degrees", [(12, 12, 12), (16, 16, 16), (32, 32, 32)])
+def test_rows_of_zeros_and_of_vanishing_squares(degrees):
+    """Zero rows of either input in every group of four, beside ordinary rows
+    and rows whose squares vanish in fp32 (all of them, or all but one)."""
+    L1, L2, Lout = degrees
+    g = torch.Generator().manual_seed(9)
+    a, b = (torch.randn((24, (L + 1) ** 2), generator=g) for L in (L1, L2))
+    a[::4] = 0.0
+    b[4:16:5] = 0.0
+    a[5] *= 1e-25
+    a[9] *= 1e-30
+    b[9] *= 1e20
+    b[13] *= 1e-25
+    b[13, 3] = 1e-18
+    a[17] *= 1e-28
+    b[17] *= 1e-25  # the products stay above 1e-38 only where the factors' scales are taken out first
+    a[17] *= 1e20
+    y = gtp.gtp_full(gtp.Plan(L1, L2, Lout), a.cuda()[:, None], b.cuda()[:, None]).cpu().numpy()[:, 0].astype(np.float64)
+    zero = (a == 0).all(1) | (b == 0).all(1)
+    assert (y[zero.numpy()] == 0).all()
+    ok = ~zero.numpy()
+    ref = O.gtp_grid(a.double().numpy()[ok], b.double().numpy()[ok], L1, L2, Lout)
+    assert O.max_rel_err(y[ok], ref) <= 1e-6
