@@ -63,7 +63,9 @@ namespace {
 // load, dividing the slab's size and both addresses.  In assembly: the
 // compiler would wait for the loads at the next LDS access of any kind; here
 // the caller waits (vmcnt) before the barrier that publishes the slab.  M0
-// holds the wave's LDS address, lane l's data go to M0 + WIDTH l.
+// holds the wave's LDS address, lane l's data go to M0 + WIDTH l.  (M0 is reserved:
+// the compiler sets it right before an instruction that needs it, keeps nothing
+// in it and takes it in no clobber list; this file's kernels use it nowhere else.)
 template <int WIDTH, int NTH, int TRIPS, typename T>
 __device__ __forceinline__ void slab_to_lds(const T* s, unsigned char* to, int n, int tid, int wave) {
   typedef __attribute__((address_space(3))) unsigned char lds_char;

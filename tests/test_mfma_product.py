@@ -133,3 +133,67 @@ def test_rows_of_zeros_and_of_vanishing_squares(degrees):
     ok = ~zero.numpy()
     ref = O.gtp_grid(a.double().numpy()[ok], b.double().numpy()[ok], L1, L2, Lout)
     assert O.max_rel_err(y[ok], ref) <= 1e-6
+
+
+def _strided(x, offset):
+    """x on the device, `offset` elements off the allocation's alignment."""
+    buf = torch.empty(x.numel() + offset, dtype=x.dtype, device="cuda")
+    v = buf[offset:].view(x.shape)
+    v.copy_(x)
+    return v
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("degrees,n", [((16, 16, 16), 4 * 768 + 3), ((16, 16, 16), 4 * 1536 + 1), ((9, 12, 10), 4 * 768 + 2),
+                                       ((32, 32, 32), 4 * 256 + 1), ((32, 32, 32), 4 * 512 + 3), ((17, 32, 20), 4 * 512 + 2)])
+@pytest.mark.parametrize("types", [(torch.float32, torch.float32), (torch.bfloat16, torch.bfloat16),
+                                   (torch.float32, torch.bfloat16)])
+def test_later_turns_of_a_workgroup(degrees, n, types):
+    """Batches past the 768 (degree 16) and 256 (32) workgroups' first groups:
+    second and third turns, their short last group staged by element, rows on
+    and off the loads' alignment; fp32 x bf16 as the gradient in x1.  Every row
+    against the workgroup-per-product kernel, the first and last products of
+    each turn against the oracle."""
+    L1, L2, Lout = degrees
+    g = torch.Generator().manual_seed(n)
+    turn = 4 * (768 if max(degrees) <= 16 else 256)
+    mixed = types[0] != types[1]
+    if mixed:  # dx1 = P_L1(dy x2) of a plan (L1', L2, Lout') with Lout' = L1, L1' = Lout
+        a = torch.randn((n, 1, (L1 + 1) ** 2), generator=g)
+        b = torch.randn((n, 1, (L2 + 1) ** 2), generator=g).to(types[1])
+    else:
+        a, b = (torch.randn((n, 1, (L + 1) ** 2), generator=g).to(types[0]) for L in (L1, L2))
+    for offset in (0, 1):
+        ad, bd = _strided(a, offset), _strided(b, offset)
+
+        def call(flags):
+            if not mixed:
+                return gtp.gtp_full(gtp.Plan(L1, L2, Lout, flags), ad, bd)
+            x1 = torch.zeros((n, 1, (Lout + 1) ** 2), dtype=types[1], device="cuda")
+            return gtp.gtp_full_backward(gtp.Plan(Lout, L2, L1, flags), x1, bd, ad, need_dx2=False)[0]
+
+        y = call(0).cpu()[:, 0].double().numpy()
+        ref = call(gtp.GTP_FORCE_GENERIC).cpu()[:, 0].double().numpy()
+        assert O.max_rel_err(y, ref) <= 2e-6  # two kernels, each within 1e-6 of the oracle
+        rows = sorted({r for t in range(0, n, turn) for r in (*range(t, t + 8), *range(t + turn - 8, t + turn))
+                       if r < n} | set(range(n - 8, n)))
+        exact = O.gtp_grid(a[rows, 0].double().numpy(), b[rows, 0].double().numpy(), L1, L2, Lout)
+        assert O.max_rel_err(y[rows], exact) <= 1e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,B,C", [(16, 1039, 3), (32, 343, 3)])
+def test_later_turns_with_channel_weights(L, B, C):
+    """The same with weights per channel: three channels move through the groups of four."""
+    K, deg = (L + 1) ** 2, O.degree_index(L)
+    g = torch.Generator().manual_seed(L)
+    a, b = (torch.randn((B, C, K), generator=g) for _ in range(2))
+    w = [1 + 0.5 * torch.randn((C, L + 1), generator=g) for _ in range(3)]
+    y = gtp.gtp_full_weighted(gtp.Plan(L, L, L), a.cuda(), b.cuda(), *(v.cuda() for v in w), per_channel=True).cpu().numpy()
+    rows = [0, 1, 2, B // 2, B // 2 + 1, B - 3, B - 2, B - 1]
+    x1, x2 = ((t[rows].double() * v.double()[:, deg]).numpy().reshape(-1, K) for t, v in ((a, w[0]), (b, w[1])))
+    ref = O.gtp_grid(x1, x2, L, L, L) * np.tile(w[2].double().numpy()[:, deg], (len(rows), 1))
+    assert O.max_rel_err(y[rows].reshape(-1, K).astype(np.float64), ref) <= 2e-6
+    generic = gtp.gtp_full_weighted(gtp.Plan(L, L, L, gtp.GTP_FORCE_GENERIC), a.cuda(), b.cuda(), *(v.cuda() for v in w),
+                                    per_channel=True).cpu().numpy()
+    assert O.max_rel_err(y.reshape(-1, K).astype(np.float64), generic.reshape(-1, K).astype(np.float64)) <= 4e-6
