@@ -463,8 +463,7 @@ hipError_t launch_chain(const DevTables& t1, const DevTables& t2, int nu, const 
 // product (and per step of a chain, through a workspace), 64000 products fp32:
 // chains of L = 3, nu = 2 / 3 / 4 to Lout = 2 574 / 1134 / 1687 -> 14 / 16 / 15
 // us (launch-bound), fourth power of L = 3 to Lout = 3 583 -> 14 us; errors
-// against 64-bit results 0.75 to 1.0 of the generic kernel's, 1.03 at the
-// fourth power of L = 1 (the order of the fp32 sums).
+// against 64-bit results 0.79 to 1.0 of the generic kernel's.
 #define GTP_SMALL_PAIRS(X) \
   X(1, 1, 1) X(2, 2, 2) X(3, 3, 3) X(4, 4, 4) X(5, 5, 5) X(6, 6, 6) X(7, 7, 7) X(8, 8, 8) X(2, 2, 3) X(3, 2, 3) X(1, 2, 2) \
       X(2, 1, 3)

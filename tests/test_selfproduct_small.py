@@ -34,3 +34,18 @@ def test_every_instantiation(L, nu, Lout, mode):
         terms = np.linalg.norm(xd, axis=1) ** nu * (4 * np.pi) ** (-(nu - 1) / 2)
         err = np.abs(y - ref).max(axis=1)
         assert (err <= 1e-5 * np.maximum(np.linalg.norm(ref, axis=1), terms)).all(), (n, dt)
+
+
+@pytest.mark.parametrize("nu,Lout,bound", [(3, 3, 1.5523e-7), (4, 1, 1.3195e-7), (4, 2, 1.4168e-7),
+                                           (4, 3, 1.5834e-7)])
+def test_error_of_low_degree_powers(nu, Lout, bound):
+    """2-norm error of fused powers of L = 1 against 64 bits over 300000 fixed
+    products: no larger than the workgroup-per-product kernel's for the same,
+    which is the bound."""
+    g = torch.Generator().manual_seed(1)
+    x = torch.randn((300000, 1, 4), generator=g) / torch.sqrt(torch.tensor([1.0, 3.0, 3.0, 3.0]))
+    y = gtp.gtp_selfproduct(x.cuda(), 1, nu, Lout, MODES["fused"]).cpu().double().numpy()[:, 0]
+    ref = O.selfproduct(x.double().numpy()[:, 0], 1, nu, Lout, "fused")
+    err = np.linalg.norm(y - ref) / np.linalg.norm(ref)
+    print(nu, Lout, f"{err:.4e}", flush=True)
+    assert err <= bound, err
