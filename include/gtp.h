@@ -33,8 +33,14 @@
  *   - Every argument is validated on the host BEFORE any HIP call; invalid
  *     arguments return GTP_ERR_INVALID_ARG and touch nothing.
  *   - Functions never throw.  gtp_last_error() gives a thread-local message.
- *   - Floating point: tables are built in fp64 on the host and rounded once to
- *     fp32; arithmetic and outputs are fp32; bf16 applies to inputs only.
+ *   - Floating point: tables are built in fp64 on the host; outputs and every
+ *     accumulation are fp32, bf16 applies to inputs only.  Tables are rounded
+ *     once to fp32 and products taken in fp32 except in two kernels that run on
+ *     the 16-bit matrix instructions, with values and tables split: products of
+ *     degrees 9..32 in two fp16 parts, 2^-23 of a value (of a row's norm where
+ *     that is larger than 2^8 times the value) at worst, and channel mixing of
+ *     degrees 1..8 in three bf16 parts, exact.  Against 64-bit results both
+ *     measure no larger errors than the fp32 kernels.
  *   - Limits: 0 <= L1, L2, Lout <= 64.  Output degrees above L1 + L2 are
  *     written as zeros.
  */
@@ -106,15 +112,25 @@ gtp_status gtp_full(gtp_plan p, const void *x1, const void *x2, gtp_dtype in_dty
 /* Channel mixing (Appendix, combination rules of features in different
  * channels, channel-mixing case):
  *   y[b, co] = sum_{c1 < C1, c2 < C2} W[co, c1, c2] GTP(x1[b, c1], x2[b, c2]),
- * O(C1 C2) full products per batch entry.  The pair products are taken by the
- * fused product kernels (outer-product indexing) into a stream-ordered
- * workspace (hipMallocAsync, at most 256 MiB, chunked over b) and combined as
- * y_b = W T_b (Co x C1C2 times C1C2 x (Lout+1)^2) on the fp32 matrix cores.
+ * O(C1 C2) full products per batch entry, in one of three ways:
+ *   - L1 = L2 = Lout in 1..8, Co <= 128, C1 C2 >= 128 and sizes at which it is
+ *     the fastest: in the sample domain, P_L(sum_{c2} F2[c2] (sum_{c1}
+ *     W[co, c1, c2] F1[c1])) with each channel's function sampled once per
+ *     entry, on the bf16 matrix cores with operands in three parts (exact fp32
+ *     values).  A channel keeps its bits down to 2^-148 of the largest value of
+ *     its batch entry, a weight down to 2^-110 of its output channel's largest;
+ *   - the other sizes of those degrees: the pair products and their combination
+ *     in one kernel per batch entry, fp32;
+ *   - all else: the pair products by the fused product kernels (outer-product
+ *     indexing) into a workspace, chunked over b, combined as y_b = W T_b (Co x
+ *     C1C2 times C1C2 x (Lout+1)^2) on the fp32 matrix cores.
+ * The weights in the kernel's layout (the first two) or the workspace are
+ * stream-ordered allocations (hipMallocAsync; the first and the last at most
+ * 256 MiB).
  * x1: [B, C1, (L1+1)^2], x2: [B, C2, (L2+1)^2] (in_dtype); W: [Co, C1, C2]
  * fp32; y: [B, Co, (Lout+1)^2] fp32, not overlapping the inputs or W.
  * C1 C2 == 0 writes zeros (x1, x2 and W may then be NULL); B Co == 0 is a
- * no-op.  The thread-per-product
- * kernel serves L1 = L2 = Lout <= 8; other degrees take the workgroup kernel. */
+ * no-op. */
 gtp_status gtp_channel_mix(gtp_plan p, const void *x1, const void *x2, gtp_dtype in_dtype, const float *W,
                            int64_t B, int64_t C1, int64_t C2, int64_t Co, float *y, void *stream);
 
