@@ -34,6 +34,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "Gaunt TP (b,c)-products/sec at L=6 fp32; % HBM/MFMA roofline on 1 MI355X"
 PEAK_FP32_TFLOPS = 157.3  # MI355X published fp32 vector / matrix peak
+PEAK_16BIT_TFLOPS = 2500.0  # dense fp16 and bf16 matrix instructions
 PEAK_HBM_GBS = 8000.0     # MI355X HBM3E
 
 # Flops per (b,c)-product of the paper's Fourier method counted for an
@@ -154,6 +155,41 @@ def escn_flops(L: int, C: int) -> float:
     per_pair = 2 * K + 2 * parts + 2 * (L + 1) + 2 + 4 * parts + 2 * K
     per_edge = sum(6 * (2 * l + 1) ** 2 + 2 * (2 * l + 1) ** 3 for l in range(L + 1))
     return 2 * rot + pairs * per_pair + per_edge / C
+
+
+def matrix_flops(kernel: str, L: int, mix=None):
+    """(fp32, 16-bit) matrix-instruction flops per product as executed, padding
+    included, of the kernels that run on both rates: k_full_mfma of degree L
+    in {16, 32} (padded triples run it whole), or k_mixq for mix = (C1, C2,
+    Co) with C1, C2 in 17.. (per pair product).  A 16x16x4 fp32 instruction is
+    2048 flops, a 16x16x32 16-bit one 16384."""
+    if kernel.startswith("k_full_mfma"):
+        tiles, waves, q = L // 16, L // 4, (3 * L + 1 + 3) // 4
+        steps = 12 if L == 16 else 20  # theta synthesis, then m = 0
+        f32 = waves * (tiles * steps + (L // 2 + 1 + 3) // 4)
+        blocks = (q + 1 + 15) // 16  # phi samples; two contractions each at 32, one at 16
+        phi = 2 * (4 * 2 * blocks * (1 if L == 16 else 2) + 4 * (2 if L == 16 else 4))
+        parts = (1 if L == 16 else 2) * (8 * waves + (L // 2 + 1 + 15) // 16 + (L // 2 + 15) // 16)
+        return f32 * 2048 / 4, (waves * phi + parts) * 16384 / 4
+    C1, C2, Co = mix
+    waves = 1 if L <= 4 else (2 if L <= 6 else 4)
+    q = (3 * L // 2 + 1) * (3 * L + 1)
+    tiles, ks, kt = ((q + 15) // 16 + waves - 1) // waves, (nsh(L) + 31) // 32, (nsh(L) + 15) // 16
+    turns, cots = (C1 + 31) // 32, (Co + 15) // 16
+    sampled = 2 * turns * ((Co + 31) // 32) * (1 + (C2 + 31) // 32) * tiles * ks
+    n = waves * (6 * sampled + 6 * turns * C2 * cots * tiles) + cots * kt * waves * 4 * 6
+    return 0.0, n * 16384 / (C1 * C2)
+
+
+def split_roof(kernel: str, L: int, ns_per_product: float, alg_flops, mix=None):
+    """The roofline entry of those kernels: the time their matrix instructions
+    take at the dense peaks of their types, as a fraction of the kernel's."""
+    f32, f16 = matrix_flops(kernel, L, mix)
+    floor_ns = (f32 / PEAK_FP32_TFLOPS + f16 / PEAK_16BIT_TFLOPS) * 1e-3
+    return {"bound": "mfma", "achieved": round((f32 + f16) / ns_per_product * 1e-3, 3),
+            "peak": round((f32 + f16) / floor_ns * 1e-3, 1), "unit": "TFLOP/s",
+            "frac": round(floor_ns / ns_per_product, 4), "fp32_matrix_flops_per_product": f32,
+            "fp16_or_bf16_matrix_flops_per_product": f16, "alg_flops_per_product": alg_flops}
 
 
 def nsh(L):
@@ -606,8 +642,8 @@ def l32_sweep(args, torch, gtp, inputs):
     the L = 32 degree sweep (B = 2048 x C = 128 products, iid N(0,1), fp32,
     the matrix-core kernel k_full_mfma<32>), with the same warmup and step
     counts, after the edge workload's timed region: its kernel time on the
-    launch stream, its fraction of the fp32 peak at the kernel's flop count
-    and its HBM traffic when the committed counters match the sources (its
+    launch stream, the part of it that its matrix instructions take at their
+    peaks (split_roof) and its HBM traffic when the committed counters match the sources (its
     parity with the oracle is the GPU tests')."""
     sa = argparse.Namespace(**vars(args))
     sa.workload, sa.L, sa.degrees, sa.products, sa.conv = "sweep", 32, "", 0, "auto"
@@ -625,13 +661,11 @@ def l32_sweep(args, torch, gtp, inputs):
     ev1.record(stream)
     torch.cuda.synchronize()
     kernel_ms = ev0.elapsed_time(ev1) / args.steps
-    achieved = alg_flops[0] * products / (kernel_ms * 1e-3) / 1e12
+    roof = split_roof("k_full_mfma", 32, kernel_ms * 1e6 / products, alg_flops[0])
     return {"workload": desc["workload"], "kernel": "k_full_mfma", "kernel_ms": round(kernel_ms, 5),
             "products_per_s": products / (kernel_ms * 1e-3),
-            "roofline": {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                         "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "alg_flops_per_product": alg_flops[0],
-                         "traffic": load_traffic("sweep_L32", "gtp_mfma.hip"),
-                         "alg_bytes_per_launch": alg_bytes * products}}
+            "roofline": dict(roof, traffic=load_traffic("sweep_L32", "gtp_mfma.hip"),
+                             alg_bytes_per_launch=alg_bytes * products)}
 
 
 def main():
@@ -734,6 +768,10 @@ def main():
         comp = {"bound": bound, "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "alg_flops_per_product": alg_flops,
                 "fft_formulation_flops_per_product": fft_flops}
+        if kname.startswith(("k_full_mfma", "k_mixq")):
+            mix = (desc["C"],) * 3 if kname == "k_mixq" else None
+            deg = desc["L1"] if mix else (16 if max(degs[0], degs[1], min(degs[2], degs[0] + degs[1])) <= 16 else 32)
+            comp = split_roof(kname, deg, kernel_ms * 1e6 / products, alg_flops, mix)
         hbm_gbs = alg_bytes * products / (kernel_ms * 1e-3) / 1e9
         hbm = {"bound": "hbm", "achieved": round(hbm_gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                "frac": round(hbm_gbs / PEAK_HBM_GBS, 4), "alg_bytes_per_product": alg_bytes}

@@ -70,3 +70,18 @@ def test_fused_backward_bookkeeping():
     for degs in ((8, 8, 8), (16, 16, 16), (0, 0, 0), (6, 6, 2), (4, 6, 5), (2, 2, 3)):
         assert not bench.fused_backward(degs)
     assert not bench.fused_backward(None)
+
+
+def test_matrix_flops_of_the_split_kernels():
+    """Instruction counts read off the kernels: per four products of degree 32
+    8 waves x 45 fp32, 8 x 96 + 134 fp16 contractions, of degree 16 4 x 15 and 4 x
+    32 + 34; per entry of the mix workload 2 waves x (2304 + 288 + 192) bf16 ones."""
+    assert bench.matrix_flops("k_full_mfma", 32) == (360 * 2048 / 4, (768 + 134) * 16384 / 4)
+    assert bench.matrix_flops("k_full_mfma (padded to L = 16)", 16) == (60 * 2048 / 4, (128 + 34) * 16384 / 4)
+    assert bench.matrix_flops("k_mixq", 6, (32, 32, 32)) == (0.0, 2 * (2304 + 288 + 192) * 16384 / 1024)
+    # at its floor a kernel is at 1, whatever the mix of rates
+    f32, f16 = bench.matrix_flops("k_full_mfma", 32)
+    ns = (f32 / 157.3 + f16 / 2500.0) * 1e-3
+    roof = bench.split_roof("k_full_mfma", 32, ns, 910860)
+    assert roof["frac"] == 1.0 and abs(roof["achieved"] - roof["peak"]) < 1.0
+    assert bench.split_roof("k_full_mfma", 32, 4 * ns, 910860)["frac"] == 0.25
