@@ -9,32 +9,6 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846264338327950288;
 
-// Gauss-Legendre nodes and weights on [-1, 1] (Newton's method on P_n).
-void gauss_legendre(int n, std::vector<double>& x, std::vector<double>& w) {
-  x.assign(n, 0.0);
-  w.assign(n, 0.0);
-  for (int i = 0; i < n; ++i) {
-    double z = std::cos(kPi * (i + 0.75) / (n + 0.5));
-    double dp = 1.0;
-    for (int it = 0; it < 100; ++it) {
-      double p0 = 1.0, p1 = z;
-      for (int k = 2; k <= n; ++k) {
-        const double p2 = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
-        p0 = p1;
-        p1 = p2;
-      }
-      const double pn = n == 0 ? 1.0 : (n == 1 ? z : p1);
-      const double pm = n == 1 ? 1.0 : p0;
-      dp = n * (z * pn - pm) / (z * z - 1.0);
-      const double dz = pn / dp;
-      z -= dz;
-      if (std::fabs(dz) < 1e-16) break;
-    }
-    x[i] = z;
-    w[i] = 2.0 / ((1.0 - z * z) * dp * dp);
-  }
-}
-
 // Real SH Y_{l,m}(theta, phi), all l <= L, index l*l + l + m.
 void real_sh(int L, double th, double ph, std::vector<double>& out) {
   std::vector<double> f(ntri(L));

@@ -11,30 +11,6 @@ namespace {
 
 const double kPiQ = 3.14159265358979323846264338327950288;
 
-// Gauss-Legendre nodes and weights on [-1, 1] (Newton's method on P_n)
-void gauss_legendre(int n, std::vector<double>& x, std::vector<double>& w) {
-  x.assign(n, 0.0);
-  w.assign(n, 0.0);
-  for (int i = 0; i < n; ++i) {
-    double z = std::cos(kPiQ * (i + 0.75) / (n + 0.5)), d = 1.0;
-    for (int it = 0; it < 100; ++it) {
-      double p0 = 1.0, p1 = z;
-      for (int k = 2; k <= n; ++k) {
-        const double p2 = ((2 * k - 1) * z * p1 - (k - 1) * p0) / k;
-        p0 = p1;
-        p1 = p2;
-      }
-      if (n == 1) p0 = 1.0;
-      d = n * (z * p1 - p0) / (z * z - 1.0);
-      const double step = p1 / d;
-      z -= step;
-      if (std::fabs(step) < 1e-16) break;
-    }
-    x[i] = z;
-    w[i] = 2.0 / ((1.0 - z * z) * d * d);
-  }
-}
-
 template <int L>
 std::vector<uint16_t> images() {
   using G = MixqGeo<L>;

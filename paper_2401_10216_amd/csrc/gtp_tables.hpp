@@ -67,6 +67,9 @@ Tables build_tables(int L1, int L2, int Lout);
 // recurrence), out[tri(l, m)].
 void theta_factors(int L, double t, double* out);
 
+// Gauss-Legendre nodes and weights on [-1, 1] (Newton's method on P_n).
+void gauss_legendre(int n, std::vector<double>& x, std::vector<double>& w);
+
 // fp64 evaluation of the sampled three-step pipeline with the tables above
 // (host check of the tables; never used by the device path).
 void host_pipeline(const Tables& t, const double* x1, const double* x2, int64_t n, double* y);
