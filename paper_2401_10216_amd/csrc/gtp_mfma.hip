@@ -31,18 +31,18 @@
 // read them for each; x comes in by 16-byte loads straight into LDS, the next
 // group's issued after B.
 //
-// Bound: issue of matrix and vector instructions together (the two do not
-// overlap on a SIMD: a 16x16x32 contraction with n vector instructions
-// measured 16 + 2.3 n cycles), about 60 % of the time; the rest is latency
-// between the five barriers of a turn, with two (L = 32) and three (L = 16)
-// waves per SIMD.  Measured against the fp32 one-wave-per-product kernel it
-// replaced (theta stages on the VALU, table reads per product): 262144
-// products of degree 32 3.59 -> 2.58 ms, 2.1M bf16 products of degree 16 5.20 ->
-// 4.57 ms, 191904 of degree 12 0.478 -> 0.400 ms; error against fp64 (2-norm)
-// 1.7e-7 -> 1.4e-7 at 32, 1.35e-7 -> 1.29e-7 at 16, 1.18e-7 -> 1.11e-7 at 12 (1.38e-7
-// and 1.19e-7 with phi tables at scale 1).  (The
-// theta synthesis by split fp16 too measured slower at L = 16, its operands'
-// split and scaling costing more than the contractions saved, and less exact.)
+// Bound: issue of matrix and vector instructions (of the SIMDs' cycles, by
+// counters: degree 32 27 % matrix, 42 % vector at four cycles each; 16 and 12 21 to
+// 22 % and 56 %), the two seldom at once on a SIMD; the rest is latency between
+// the five barriers of a turn, with two (L = 32) and three (L = 16) waves per
+// SIMD.  Measured against the fp32 one-wave-per-product kernel it replaced
+// (theta stages on the VALU, table reads per product): 262144 products of
+// degree 32 3.58 -> 2.59 ms, 2.1M bf16 products of degree 16 5.20 -> 4.60 ms, 191904
+// of degree 12 0.479 -> 0.402 ms; error against fp64 (2-norm) 1.67e-7 -> 1.38e-7 at
+// 32, 1.35e-7 -> 1.29e-7 at 16, 1.18e-7 -> 1.11e-7 at 12 (1.38e-7 and 1.19e-7 with
+// phi tables at scale 1).  (The theta synthesis by split fp16 too measured slower
+// at L = 16, its operands' split and scaling costing more than the contractions
+// saved, and less exact.)
 #include <type_traits>
 #include <utility>
 
@@ -616,6 +616,7 @@ hipError_t launch_typed(const DevTables& t, const void* x1, const void* x2, int6
     const int vecx = reinterpret_cast<uintptr_t>(a) % (sizeof(T1) == 4 ? 16 : 4) == 0 &&
                      reinterpret_cast<uintptr_t>(b) % (sizeof(T2) == 4 ? 16 : 4) == 0;
     const int vecy = reinterpret_cast<uintptr_t>(yy) % 16 == 0 && ko <= KG::K;
+    // as many workgroups as MI355X's 256 CUs hold (a multiple of 8; any number works)
     constexpr int64_t most = 256 * KG::WGS;
     hipLaunchKernelGGL((k_full_mfma<L, T1, T2, WGT>), dim3(unsigned(ng < most ? ng : most)), dim3(KG::NTH), 0, s, a, b,
                        yy, nn, ng, ng < most ? ng : most, t, w, k1, k2, ko, vecx, vecy);

@@ -25,8 +25,9 @@
 //
 // Bound: issue of the matrix instructions (L = 6, C1 = C2 = Co = 32, per wave
 // and batch entry: 2304 over c1, 288 for the sampling, 192 for the analysis, 16
-// cycles each) and of the vector instructions beside them, mostly the
-// multiply-adds over c2 and the splits; the two do not overlap on a SIMD.
+// cycles each, 68 % of the SIMDs' cycles by counters) and of the vector
+// instructions beside them (25 %), mostly the multiply-adds over c2 and the
+// splits; the two do not overlap on a SIMD.
 // Waves of their own columns rather than of their own channels: F1, F2 and the
 // sums then never leave the wave until the analysis.  Loads go out together
 // (staged rows, tiles of the quadrature's values, weights channels ahead).
