@@ -796,7 +796,7 @@ def main():
 
     metric = METRIC
     if args.workload == "mix":
-        metric = "channel-mixing Gaunt TP (b,c1,c2) pair-products/sec at L=6 fp32, C=32; % ALU roofline on 1 MI355X"
+        metric = "channel-mixing Gaunt TP (b,c1,c2) pair-products/sec at L=6 fp32, C=32; % MFMA roofline on 1 MI355X"
     if args.escn:
         metric = "equivariant convolution (b,c)-products/sec at L=6 fp32, rotated edge frame; % ALU roofline on 1 MI355X"
     if args.weighted:

@@ -8,6 +8,8 @@ three bf16 parts hold fp32 values exactly, products leave out 2^-24 of a term at
 worst, and the four sums of a result (samples, over c1, over c2, analysis) round
 at 2^-24 of their partial sums, a handful of times each: about ten times 2^-24,
 6e-7, were they to add up (seen: 1e-7, as for the fp32 pair products)."""
+import os
+
 import numpy as np
 import pytest
 
@@ -183,3 +185,38 @@ def test_the_way_that_pays_is_taken(monkeypatch, L, B, C1, C2, Co):
     hooked = gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W)
     monkeypatch.delenv("GTP_TEST_MIX")
     assert torch.equal(gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W), hooked)
+
+
+@pytest.mark.parametrize("L", range(1, 9))
+@pytest.mark.parametrize("B,C1,C2,Co,dt", [(5, 16, 12, 16, torch.float32), (3, 40, 9, 33, torch.bfloat16),
+                                           (6, 17, 33, 17, torch.float32)])
+def test_reads_no_lds_it_has_not_written(L, B, C1, C2, Co, dt):
+    """The same bits from the build whose kernels fill their LDS with NaN first."""
+    g = torch.Generator().manual_seed(L)
+    x1, x2 = (torch.randn((B, c, (L + 1) ** 2), generator=g).to(dt).cuda() for c in (C1, C2))
+    W = torch.randn((Co, C1, C2), generator=g).cuda()
+    y = gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W)
+    with gtp.use_library(os.path.join(os.path.dirname(gtp.__file__), "libgtp_poison.so")):
+        z = gtp.gtp_channel_mix(gtp.Plan(L, L, L), x1, x2, W)
+        torch.cuda.synchronize()
+    assert torch.isfinite(y).all() and torch.equal(y, z)
+
+
+@pytest.mark.parametrize("L,C1,C2,Co", [(1, 33, 20, 17), (6, 32, 32, 32), (8, 16, 40, 5)])
+def test_several_streams(L, C1, C2, Co):
+    """Calls on four streams at once, each with its own inputs: the results of one after the other."""
+    g = torch.Generator(device="cuda").manual_seed(L)
+    plan = gtp.Plan(L, L, L)
+    jobs = [[torch.randn(s, generator=g, device="cuda") for s in ((37, C1, (L + 1) ** 2), (37, C2, (L + 1) ** 2),
+                                                                 (Co, C1, C2))] for _ in range(4)]
+    want = [gtp.gtp_channel_mix(plan, *j) for j in jobs]
+    streams = [torch.cuda.Stream() for _ in jobs]
+    torch.cuda.synchronize()
+    got = []
+    for _ in range(5):
+        for s, j in zip(streams, jobs):
+            with torch.cuda.stream(s):
+                got.append(gtp.gtp_channel_mix(plan, *j))
+    torch.cuda.synchronize()
+    for i, y in enumerate(got):
+        assert torch.equal(y, want[i % 4]), i
