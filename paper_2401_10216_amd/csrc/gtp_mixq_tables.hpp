@@ -45,12 +45,12 @@ inline int64_t mixq_steps(int64_t C) { return C <= 16 ? 3 : 6 * ((C + 31) / 32);
 // serves many pairs and outputs: 8192 entries of 32 x 32 -> 32 at L = 6 526 us
 // against 1018, but 2048 of 256 x 2 -> 32 at L = 1 102 against 35, 16384 of 16
 // x 16 -> 128 at L = 7 (a third again per output block) 2.6 times the pairs'.
-// Both times in us from per-degree constants fitted to 1092 measured sizes (128
-// to 4096 pairs, 8 to 128 outputs, 16 to 16384 entries) within 20 %: a fixed
-// part, which a small batch pays, and one per entry; the sample domain has to
-// be 1.2 times faster by them, and at none of those sizes did it then measure
-// slower by more than 3 %.  Under 8 channels in one input (padded to 16 or 32)
-// the fit does not hold.
+// Both times in us from per-degree constants fitted to 1920 measured sizes (544
+// shapes of 128 to 4096 pairs and 8 to 128 outputs at 16 to 16384 entries) within
+// 25 %: a fixed part, which a small batch pays, and one per entry; the sample
+// domain has to be 1.2 times faster by them, and at none of those sizes did it
+// then measure slower by more than 5 %.  Under 8 channels in one input (padded
+// to 16 or 32) the fit does not hold.
 inline bool mixq_pays(int L, int64_t B, int64_t C1, int64_t C2, int64_t Co, int nct) {
   struct Cost {
     double chunk_us, chunk, tile;     // pairs: 256 of them, fixed; per entry (ns), and per 16 outputs

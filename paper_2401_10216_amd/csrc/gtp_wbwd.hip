@@ -16,12 +16,12 @@
 // read again while they are still in the caches, and neither u1, u2 nor z goes
 // to memory.
 //
-// Bound: HBM and the core's arithmetic about equally (three products per five
-// rows moved).  Before, the three products went through memory to separate
-// reductions, 17 rows in all: forward and backward of 1M products of degree 4
-// with per-channel weights 0.660 -> 0.275 ms; bf16 inputs, which had no weighted
-// fp32 x bf16 kernel and took the workgroup kernel, 26k products of degree 7
-// 1.10 -> 0.085 ms.
+// Bound: vector issue (73 % of the SIMDs' cycles at degree 4 by counters) and HBM
+// (three products per five rows moved).  Before, the three products went through
+// memory to separate reductions, 17 rows in all: forward and backward of 1M
+// products of degree 4 with per-channel weights 0.66 -> 0.28 ms; bf16 inputs,
+// which had no weighted fp32 x bf16 kernel and took the workgroup kernel, 65536
+// products of degree 8 3.01 -> 0.12 ms.
 #include "gtp_small_core.hpp"
 #include "gtp_wbwd.hpp"
 
