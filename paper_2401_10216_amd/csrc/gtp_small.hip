@@ -306,13 +306,19 @@ hipError_t launch_pairs_one(const DevTables& t, const void* x1, int it1, const v
 // to the next through y itself (each lane reads back what it wrote; the
 // lines stay in L2), so no accumulator is live during the products.  Only
 // x1, x2, W and y touch HBM.
+// FINE (from 128 pairs): 32 pairs at a time are summed from zero, those sums to
+// the round's, the rounds' to y, instead of every K-step rounding the whole sum
+// so far: error against 64-bit results at L = 6 2.3e-7 -> 1.5e-7 at 128 pairs, 5.8e-7
+// -> 1.6e-7 at 1024, 1.1e-6 -> 1.7e-7 at 4096, for 0 to 5 % of time (11 to 16 % at
+// L <= 4 and 128 outputs; runs of 16 pairs took 30 % there, and an outer loop over
+// runs 40 %).
 typedef float mixv4 __attribute__((ext_vector_type(4)));
 constexpr int kMixThreads = 256;
 // waves per SIMD of the fused mix: the thread-per-product core's budget,
 // except at L = 8 where the 81 KB tile admits one workgroup per CU anyway
 constexpr int mix_waves(int L) { return L == 8 ? 1 : small_waves(L, L, L); }
 
-template <int L, typename TIn, int NCT>
+template <int L, typename TIn, int NCT, bool FINE>
 __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix_waves(L)))) void k_mix_fused(
     const TIn* __restrict__ x1, const TIn* __restrict__ x2, const float* __restrict__ WB, float* __restrict__ y,
     int64_t C1, int64_t C2, int Co, int64_t P, const float* __restrict__ ST, int ntS, const float* __restrict__ WT,
@@ -349,7 +355,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix
     // this wave's partial sums of the previous rounds (output rows k0 + 4 g +
     // rr of channel 16 ct + i) and its first weight block, requested before
     // the barrier so that they arrive while the other waves finish
-    mixv4 macc[KTW][NCT], bw[KTW][NCT];
+    mixv4 macc[KTW][NCT], bw[KTW][NCT], yp[FINE ? KTW : 1][FINE ? NCT : 1];
     const float* const wb = WB + ((r * 16) * CoB + i) * 16 + g * 4;
     cfor<0, KTW>([&](auto TT) {
       constexpr int t = decltype(TT)::value;
@@ -360,7 +366,9 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
           const int k = k0 + 4 * g + rr;
-          macc[t][ct][rr] = (r > 0 && co < Co && k < Kd) ? y[(b * Co + co) * Kd + k] : 0.0f;
+          const float v = (r > 0 && co < Co && k < Kd) ? y[(b * Co + co) * Kd + k] : 0.0f;
+          macc[t][ct][rr] = FINE ? 0.0f : v;
+          if constexpr (FINE) yp[t][ct][rr] = v;
         }
         bw[t][ct] = *reinterpret_cast<const mixv4*>(wb + ct * 256);
       }
@@ -373,6 +381,8 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix
         const int ka = k0 + i < Kd ? k0 + i : Kd - 1;
         const bool kok = k0 + i < Kd;
         mixv4 bn[NCT];
+        constexpr int RUN = 2;  // blocks of 16 pairs summed from zero (FINE)
+        mixv4 run[FINE ? NCT : 1];
 #pragma unroll 2
         for (int q = 0; q < 16; ++q) {
           float a[4];
@@ -388,10 +398,16 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix
 #pragma unroll
           for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-            for (int ct = 0; ct < NCT; ++ct)
-              macc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[sp], bw[t][ct][sp], macc[t][ct], 0, 0, 0);
+            for (int ct = 0; ct < NCT; ++ct) {
+              mixv4& s = FINE ? run[FINE ? ct : 0] : macc[t][ct];
+              if (FINE && sp == 0 && q % RUN == 0) s = mixv4{0.0f, 0.0f, 0.0f, 0.0f};
+              s = __builtin_amdgcn_mfma_f32_16x16x4f32(a[sp], bw[t][ct][sp], s, 0, 0, 0);
+            }
 #pragma unroll
-          for (int ct = 0; ct < NCT; ++ct) bw[t][ct] = bn[ct];
+          for (int ct = 0; ct < NCT; ++ct) {
+            if (FINE && q % RUN == RUN - 1) macc[t][ct] += run[FINE ? ct : 0];
+            bw[t][ct] = bn[ct];
+          }
         }
 #pragma unroll
         for (int ct = 0; ct < NCT; ++ct) {
@@ -399,6 +415,7 @@ __global__ __launch_bounds__(kMixThreads) __attribute__((amdgpu_waves_per_eu(mix
 #pragma unroll
           for (int rr = 0; rr < 4; ++rr) {
             const int k = k0 + 4 * g + rr;
+            if constexpr (FINE) macc[t][ct][rr] += yp[t][ct][rr];
             if (co < Co && k < Kd) y[(b * Co + co) * Kd + k] = macc[t][ct][rr];
           }
         }
@@ -415,18 +432,31 @@ hipError_t launch_mix_fused_typed(const DevTables& t, const void* x1, const void
   const int64_t P = C1 * C2;
   const TIn* a = static_cast<const TIn*>(x1);
   const TIn* c = static_cast<const TIn*>(x2);
+  const bool fine = P >= 128;  // shorter sums keep their order, and their bits
   switch (nct) {
     case 1:
-      hipLaunchKernelGGL((k_mix_fused<L, TIn, 1>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      if (fine)
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 1, true>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      else
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 1, false>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
       break;
     case 2:
-      hipLaunchKernelGGL((k_mix_fused<L, TIn, 2>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      if (fine)
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 2, true>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      else
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 2, false>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
       break;
     case 4:
-      hipLaunchKernelGGL((k_mix_fused<L, TIn, 4>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      if (fine)
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 4, true>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      else
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 4, false>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
       break;
     case 8:
-      hipLaunchKernelGGL((k_mix_fused<L, TIn, 8>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      if (fine)
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 8, true>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
+      else
+        hipLaunchKernelGGL((k_mix_fused<L, TIn, 8, false>), grid, block, 0, s, a, c, WB, y, C1, C2, Co, P, t.ST, t.ntS, t.WT, t.ntW);
       break;
     default: return hipErrorInvalidValue;
   }
