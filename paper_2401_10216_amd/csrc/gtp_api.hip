@@ -35,7 +35,7 @@ struct gtp_plan_ {
   int device = -1;
   int conv = GTP_CONV_DFT;
   bool force_generic = false;
-  bool sampled_mix = false;  // test hook
+  int mix_way = 0;  // test hook (mix_hook)
   gtp::Tables tab;
   std::vector<uint16_t> mfx;  // and the index images of the plan's own row lengths (padded plans too)
   gtp::MfmaImages mf;         // operand images of the split-operand kernel (L1 = L2 = Lout in {16, 32})
@@ -113,12 +113,13 @@ long fail_alloc_hook(bool* host) {
   const long n = std::strtol(v, &end, 10);
   return (end && *end == '\0' && n >= 0) ? n : -1;
 }
-// Test hook: GTP_TEST_MIX=sampled, read at every plan creation, has the plan's
-// channel mixing take the sample domain wherever its kernels exist, whatever
-// the sizes that pay; unset in normal use.
-bool sampled_mix_hook() {
+// Test hook: GTP_TEST_MIX=sampled or pairs, read at every plan creation, has the
+// plan's channel mixing take the sample domain wherever its kernels exist (1), or
+// the pair products (-1), whatever the sizes that pay; unset (0) in normal use.
+int mix_hook() {
   const char* v = std::getenv("GTP_TEST_MIX");
-  return v && std::strcmp(v, "sampled") == 0;
+  if (!v) return 0;
+  return std::strcmp(v, "sampled") == 0 ? 1 : std::strcmp(v, "pairs") == 0 ? -1 : 0;
 }
 bool dtype_ok(gtp_dtype d) { return d == GTP_F32 || d == GTP_BF16; }
 
@@ -276,7 +277,7 @@ gtp_status make_plan(gtp_plan* out, int L1, int L2, int Lout, unsigned flags, in
   p->host_only = (flags & GTP_PLAN_HOST_ONLY) != 0;
   p->force_generic = (flags & kForceGeneric) != 0;
   p->conv = conv == GTP_CONV_AUTO ? int(auto_conv(L1, L2, Lout)) : int(conv);
-  p->sampled_mix = sampled_mix_hook();
+  p->mix_way = mix_hook();
   bool fail_host = false;
   const long fail_dev = fail_alloc_hook(&fail_host);
   try {
@@ -571,14 +572,14 @@ gtp_status gtp_channel_mix(gtp_plan p, const void* x1, const void* x2, gtp_dtype
     // domain (gtp_mixq.hip: error against 64-bit results 7.5e-8 to 1.0e-7 at 128
     // pairs, 1.0e-7 to 1.2e-7 at 1024) where that is faster and its weights'
     // operands, three or more times W, stay within the other workspaces' bound;
-    // else the pair products themselves (k_mix_fused: 1.1e-7 at 16, 1.5e-7 to
-    // 1.8e-7 at 64, 2.2e-7 at 128, 5.8e-7 at 1024).
+    // else the pair products themselves (k_mix_fused: 1.1e-7 at 16 pairs, 1.8e-7
+    // at 64, and 1.4e-7 to 1.8e-7 from 128 to 4096).
     constexpr int64_t kMixqPairs = 128, kMixqWork = int64_t(256) << 20;
     int64_t nwb = 0;
     if (!mul_ok((P + 255) / 256 * 256, int64_t(16) * nct, &nwb) || nwb > INT64_MAX / 4)
       return fail(GTP_ERR_INVALID_ARG, "C1*C2 too large");
     const bool mixq = P >= kMixqPairs && P <= kMixqWork && C1 * K <= 0x7fffffff && C2 * K <= 0x7fffffff &&
-                      (p->sampled_mix || gtp::mixq_pays(p->L1, B, C1, C2, Co, nct)) &&
+                      (p->mix_way ? p->mix_way > 0 : gtp::mixq_pays(p->L1, B, C1, C2, Co, nct)) &&
                       std::max(gtp::mixq_work_bytes(Co, C1, C2), gtp::mixq_work_bytes(Co, C2, C1)) <= kMixqWork;
     // the matrix cores contract over the channels of one input; the cheaper of the two
     const bool swap = mixq && gtp::mixq_steps(C2) * C1 < gtp::mixq_steps(C1) * C2;

